@@ -37,7 +37,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-KERNEL_SOURCES = ["engine.h", "kernels.h", "kernels2.h", "radix.h", "radix_gen.h", "fcsdnn.hip"]
+KERNEL_SOURCES = ["engine.h", "kernels.h", "linemat.h", "kernels2.h", "radix.h", "radix_gen.h", "fcsdnn.hip"]
 COPY_MIB = 1024
 
 
@@ -76,8 +76,8 @@ def recorded_traffic(kernel, npts):
 # again (FP32)
 FILTER_BYTES = 64
 
-PASS_KERNEL = {"A": "k_dev_diff2<1>", "B1": "k_passB1", "B2": "k_passB2", "C": "k_passC", "Bf": "k_passB",
-               "Bw": "k_passB4", "stage": "k_stage"}
+PASS_KERNEL = {"A": "k_dev_diff2<1>", "B1": "k_mat_B", "B2": "k_mat_B2", "C": "k_passC", "Bf": "k_mat_B",
+               "Bw": "k_mat_B", "stage": "k_stage"}
 # passes of a stage under each schedule (Bf: passes B1 and B2 in one launch)
 SCHED_PASSES = {"split": ["A", "B1", "B2", "C"], "fused": ["A", "Bf", "C"], "persistent": ["A", "Bf", "C"],
                 "fused_wide": ["A", "Bw", "C"]}

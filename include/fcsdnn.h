@@ -128,10 +128,13 @@ enum {
  * FCSD_LDS_BUDGET environment variable at creation) and the workgroup size
  * (64, 128, 256, 512 or 1024 threads; default 256); and the launch order of
  * all tiles.  Larger budgets mean more lines per tile, fewer workgroups per
- * compute unit; larger workgroups put more threads on each line.  A tile
+ * compute unit; larger workgroups put more threads on each line.  (The
+ * passes of lines whose derivative runs as a matrix product take a fixed
+ * workgroup size and, of the first or third budget, what tiles of 16 or 32
+ * columns need; 80 KB unless tuned.)  A tile
  * whose smallest storage-aligned size exceeds its budget takes more (a
  * launch takes its largest tile's LDS); the q2 tiles of four complex lines
- * per grid line (the wide fused pass, the reverse mode's q2 pass) share the
+ * per grid line (the reverse mode's q2 pass) share the
  * third budget and workgroup size, and when their tiles exceed it they are
  * built for the device's whole LDS per workgroup with 1024 threads.
  * Synchronises the context's stream and drops captured step graphs.  Returns
@@ -148,10 +151,9 @@ enum {
   FCSD_SCHED_PERSISTENT = 2, /* one launch per stage: resident workgroups take A, B and C
                                 tiles from a queue; a B tile starts once its patch's A
                                 tiles are done, a C tile once its patch's B tiles are */
-  FCSD_SCHED_FUSED_WIDE = 3   /* three launches like FCSD_SCHED_FUSED, the q2 pass on tiles
-                                that hold all eight H fields in LDS (four complex lines per
-                                grid line, half as many lines per tile); FCSD_EINVAL when
-                                such tiles do not fit a workgroup's LDS */
+  FCSD_SCHED_FUSED_WIDE = 3   /* three launches like FCSD_SCHED_FUSED; FCSD_EINVAL when tiles of
+                                four complex lines per grid line do not fit a workgroup's
+                                LDS */
 };
 /* Select the schedule of `set` for fcsd_rhs, fcsd_stage and fcsd_step (the
  * per-patch and per-pass entry points always launch the passes one by one).
@@ -160,12 +162,12 @@ enum {
  * four components, fused with the q2 transpose of its output, except with
  * FCSD_SCHED_SPLIT (and on sets with walls); the results agree to FP32
  * rounding (the transposes' tail folds sum in a tile-dependent order).
- * The persistent schedule uses the q1 tile set's workgroup size for every
- * task and the larger of the two tile sets' LDS plus 16 bytes (the queue
- * slot); it needs that to fit the device's LDS per workgroup (budgets of at
- * most 160 KB - 16), else FCSD_EINVAL.  It is used for every stage of sets
- * without wall sides; stages of sets with walls (whose energy rule runs
- * between passes A and B) fall back to the fused schedule.  A dependency
+ * The persistent schedule needs the tile sets' LDS plus 16 bytes (the queue
+ * slot) to fit the device's LDS per workgroup (budgets of at most 160 KB -
+ * 16), else FCSD_EINVAL.  It is used for every stage of sets without wall
+ * sides all of whose lines run as matrix products; stages of other sets (on
+ * walls the energy rule runs between passes A and B) fall back to the fused
+ * schedule.  A dependency
  * wait that gives up (never expected: it would take about a second) sets
  * bit 0 of the word fcsd_stage_errors reads.  Synchronises the context's
  * stream and drops captured step graphs. */
@@ -518,8 +520,8 @@ fcsd_status fcsd_stage_adj(fcsd_ctx* ctx, const fcsd_set* set, int stage, const 
 /* One of the four passes of fcsd_stage (0: q1 derivatives of the state,
  * 1: q2 derivatives and the combined fluxes H, 2: q2 derivatives of H,
  * 3: q1 derivatives of H and the register update), or 4: passes 1 and 2 in
- * one launch (the fused schedule's q2 pass), 5: the same on tiles holding
- * all eight H fields (the wide fused schedule's), for timing and profiling.
+ * one launch (the fused schedule's q2 pass), 5: the same (the wide fused
+ * schedule's), for timing and profiling.
  * Running passes 0..3 (or 0, 4, 3) in order equals one fcsd_stage call;
  * with mu == NULL passes 0 and 1 together are the pointwise inviscid H. */
 fcsd_status fcsd_stage_pass(fcsd_ctx* ctx, const fcsd_set* set, int pass, int stage, const float* u0,

@@ -24,7 +24,7 @@ from . import api
 
 SET_PASSES = ((0, 3), (2,), (1,))   # tile set -> passes timed (A+C, B2, B1)
 FUSED_PASSES = ((0, 3), (2,), (4,))  # the same with the fused B pass on the third set
-WIDE_PASSES = ((0, 3), (2,), (5,))   # the fused B pass with all H fields in LDS
+WIDE_PASSES = ((0, 3), (2,), (5,))   # the wide schedule's B pass
 PERSISTENT_BUDGET = 163840 - 256    # leaves room for the persistent kernel's queue slot
 DEFAULT_BUDGETS = (24576, 32768, 49152, 65536, 81920, 98304, 131072, 163840)
 DEFAULT_THREADS = (256, 512, 1024)

@@ -55,6 +55,10 @@ struct PlanDev {
   int patch;     // patch index
   int periodic;  // C == 0
   int nb1;       // 0: row-major patch storage; else 8x4 blocks, nb1 per block row
+  int mat;       // the derivative runs as a matrix product (linemat.h)
+  int mrb, mks;  // its table: row blocks of 16 position pairs, K steps of 32 difference pairs
+  int mes;       // the table holds the matrix times 2^mes
+  long long mt;  // offset of the table (uint4)
   long long off; // patch offset in a plane
 };
 

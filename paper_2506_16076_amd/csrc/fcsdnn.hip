@@ -104,6 +104,9 @@ struct TileSet {
 struct DirPlan {
   std::vector<PlanDev> plans;             // one per patch
   TileSet ts[3];                          // one / two / four complex lines per grid line
+  TileSet ms;                             // lines whose derivative runs as a matrix product (linemat.h)
+  bool mat_large = false;                 // by the kernels for large lines
+  bool any_fft = false;                   // lines that run as transforms
   std::vector<long long> ext_off;         // per plan
   long long ext_plane = 0;
   PlanDev* d_plans = nullptr;
@@ -121,6 +124,7 @@ struct fcsd_set {
   DirPlan dir[2];
   float2* d_tw = nullptr;
   float2* d_km = nullptr;
+  uint4* d_mt = nullptr;                  // derivative tables of the plans that run as matrix products
   float2* d_kf = nullptr;                 // spectral filter factors (fcsd_set_filter)
   int filter_on = 0;
   double filter_alpha = 0.0;
@@ -173,7 +177,8 @@ struct fcsd_set {
   int ntasks = 0;
   unsigned* d_ctr = nullptr;              // queue head, 2 npatch counters, then the error word
   unsigned* d_need = nullptr;             // 2 npatch: A tiles, B tiles per patch
-  unsigned stage_grid = 0;                // resident workgroups of the persistent launch
+  unsigned stage_grid = 0;                // resident workgroups of the persistent launch (0: it runs fused)
+  bool persistent_ok = false;             // the persistent schedule can be selected
   size_t stage_lds = 0;
   int stage_threads = 0;
   bool wide_ok = false;                   // the q2 tiles of four complex lines per grid line fit the LDS
@@ -218,6 +223,7 @@ PassArgs base_args(const fcsd_set* s, int dir) {
   a.tiles = s->dir[dir - 1].ts[0].d_tiles;
   a.tw = s->d_tw;
   a.km = s->d_km;
+  a.mt = s->d_mt;
   a.kf = s->d_kf;
   a.aq = s->d_aq;
   a.dq = s->d_dq;
@@ -259,6 +265,43 @@ fcsd_status launch_lines(const fcsd_set* s, int dir, K kern, PassArgs a, int pat
   if (grid == 0) return FCSD_OK;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(D.threads), lds, s->ctx->stream, a);
   return launch_check(s->ctx, "line kernel");
+}
+
+// A forward line pass as kernels: of lines that run as matrix products (small
+// lines, large lines) and of lines that run as transforms.
+typedef void (*LineKernel)(PassArgs);
+struct ForwardKernels {
+  LineKernel mat[2], fft;
+};
+template <int DIR>
+ForwardKernels diff_kernels(LineKernel fft) {
+  return ForwardKernels{{k_mat_diff<MatSmall, DIR>, k_mat_diff<MatLarge, DIR>}, fft};
+}
+
+// Launch a forward line pass along dir over the set's tiles, or one patch's,
+// either kind of line by its kernel (the transform's tiles hold `fields`
+// complex lines per grid line).
+fcsd_status launch_forward(const fcsd_set* s, int dir, const ForwardKernels& K, PassArgs a, int patch = -1,
+                           int fields = 1) {
+  const DirPlan& D = s->dir[dir - 1];
+  const TileSet& M = D.ms;
+  a.plans = D.d_plans;
+  unsigned grid = (unsigned)M.tiles.size();
+  size_t lds = M.lds;
+  a.tiles = M.d_tiles;
+  if (patch >= 0) {
+    a.tiles = M.d_tiles_bp + M.patch_begin[patch];
+    grid = (unsigned)(M.patch_begin[patch + 1] - M.patch_begin[patch]);
+    lds = M.patch_lds[patch];
+  }
+  if (grid > 0) {
+    hipLaunchKernelGGL(K.mat[D.mat_large], dim3(grid), dim3(M.threads), lds, s->ctx->stream, a);
+    fcsd_status st = launch_check(s->ctx, "matrix line kernel");
+    if (st) return st;
+  }
+  if (patch < 0 ? !D.any_fft : D.plans[patch].mat != 0) return FCSD_OK;
+  a.fft_only = 1;
+  return launch_lines(s, dir, K.fft, a, patch, fields);
 }
 
 fcsd_status check_set(fcsd_ctx* ctx, const fcsd_set* s, int64_t plane) {
@@ -462,47 +505,9 @@ size_t default_lds_budget() {
 // L2) round-robin by workgroup index.
 constexpr int kXcd = 8;
 
-void build_tileset(const std::vector<PlanDev>& plans, TileSet& D, size_t budget, int order, int fields, int align,
-                   int d) {
-  D.tiles_by_patch.clear();
-  D.patch_begin.assign(1, 0);
-  D.patch_lds.clear();
-  D.lds = 0;
-  std::vector<long long> pcost;
-  for (size_t p = 0; p < plans.size(); ++p) {
-    const PlanDev& P = plans[p];
-    // LDS: lines (L x ld), twiddle and multiplier tables (2 L), end samples (2d x ld)
-    const size_t tables = (size_t)P.L * 2 * sizeof(float2);
-    const size_t per_ld = sizeof(float2) * ((size_t)P.L + 2 * (size_t)d);
-    int nlmax = budget > tables ? (int)((budget - tables) / per_ld) - 1 : 1;
-    nlmax = std::max(1, std::min(kMaxTile, nlmax)) / fields;
-    nlmax = std::max(align, nlmax / align * align);  // blocked storage: tiles start on block edges
-    const int nt = (P.nlines + nlmax - 1) / nlmax;
-    const int nl = ((P.nlines + nt - 1) / nt + align - 1) / align * align;
-    size_t plds = 0;
-    long long cost = 0;
-    for (int t = 0; t < nt; ++t) {
-      TileDev T;
-      T.plan = (int)p;
-      T.line0 = t * nl;
-      T.nl = std::min(nl, P.nlines - T.line0);
-      if (T.nl <= 0) continue;
-      // odd row stride (the line-fastest FFT accesses and the position-fastest
-      // loads both free of LDS bank conflicts), or the even one when only
-      // that keeps the tile within the budget: two workgroups per CU instead
-      // of one are worth far more than the conflicts (the q2 tiles of two
-      // complex lines per grid line on the longest lines: 83 KB odd, 79 KB even)
-      T.ld = (fields * T.nl) | 1;
-      if (per_ld * T.ld + tables > budget && per_ld * (fields * T.nl) + tables <= budget) T.ld = fields * T.nl;
-      D.tiles_by_patch.push_back(T);
-      plds = std::max(plds, per_ld * T.ld + tables);
-      cost += (long long)P.L * T.nl;
-    }
-    D.patch_begin.push_back((int)D.tiles_by_patch.size());
-    D.patch_lds.push_back(plds);
-    D.lds = std::max(D.lds, plds);
-    pcost.push_back(cost);
-  }
+// Launch order of a tile set from its patch-contiguous tiles; pcost: the work
+// of each patch's tiles.
+void order_tiles(const std::vector<PlanDev>& plans, TileSet& D, int order, const std::vector<long long>& pcost) {
   if (order == FCSD_ORDER_LPT) {
     // longest tile first over all patches
     D.tiles = D.tiles_by_patch;
@@ -558,20 +563,155 @@ void build_tileset(const std::vector<PlanDev>& plans, TileSet& D, size_t budget,
     for (size_t k = 0; k < lst[x].size(); ++k) D.tiles[k * kXcd + x] = lst[x][k];
 }
 
+void build_tileset(const std::vector<PlanDev>& plans, TileSet& D, size_t budget, int order, int fields, int align,
+                   int d) {
+  D.tiles_by_patch.clear();
+  D.patch_begin.assign(1, 0);
+  D.patch_lds.clear();
+  D.lds = 0;
+  std::vector<long long> pcost;
+  for (size_t p = 0; p < plans.size(); ++p) {
+    const PlanDev& P = plans[p];
+    // LDS: lines (L x ld), twiddle and multiplier tables (2 L), end samples (2d x ld)
+    const size_t tables = (size_t)P.L * 2 * sizeof(float2);
+    const size_t per_ld = sizeof(float2) * ((size_t)P.L + 2 * (size_t)d);
+    int nlmax = budget > tables ? (int)((budget - tables) / per_ld) - 1 : 1;
+    nlmax = std::max(1, std::min(kMaxTile, nlmax)) / fields;
+    nlmax = std::max(align, nlmax / align * align);  // blocked storage: tiles start on block edges
+    const int nt = (P.nlines + nlmax - 1) / nlmax;
+    const int nl = ((P.nlines + nt - 1) / nt + align - 1) / align * align;
+    size_t plds = 0;
+    long long cost = 0;
+    for (int t = 0; t < nt; ++t) {
+      TileDev T;
+      T.plan = (int)p;
+      T.line0 = t * nl;
+      T.nl = std::min(nl, P.nlines - T.line0);
+      if (T.nl <= 0) continue;
+      // odd row stride (the line-fastest FFT accesses and the position-fastest
+      // loads both free of LDS bank conflicts), or the even one when only
+      // that keeps the tile within the budget: two workgroups per CU instead
+      // of one are worth far more than the conflicts (the q2 tiles of two
+      // complex lines per grid line on the longest lines: 83 KB odd, 79 KB even)
+      T.ld = (fields * T.nl) | 1;
+      if (per_ld * T.ld + tables > budget && per_ld * (fields * T.nl) + tables <= budget) T.ld = fields * T.nl;
+      D.tiles_by_patch.push_back(T);
+      plds = std::max(plds, per_ld * T.ld + tables);
+      cost += (long long)P.L * T.nl;
+    }
+    D.patch_begin.push_back((int)D.tiles_by_patch.size());
+    D.patch_lds.push_back(plds);
+    D.lds = std::max(D.lds, plds);
+    pcost.push_back(cost);
+  }
+  order_tiles(plans, D, order, pcost);
+}
+
+// Lines whose derivative runs as a matrix product (linemat.h), a rule on the
+// set and the line, so that every tiling, schedule and entry point of a set
+// computes the same bits:
+//   - extensions of up to kMatMax points (the work grows with the length, the
+//     transform's with its logarithm);
+//   - q1 lines of sets of at most kMatPoints points, and those whose length has
+//     no radix plan (their transform is twice as long): passes A and C of 3.9 M
+//     points take 51 .. 70 ps a point as products against 61 .. 79 as
+//     transforms (sides 101 .. 512), of the 15.8 M points of 200 uneven patches
+//     829 against 772 us (there the transform's larger tiles fill the chip, and
+//     the products stream their tables from beyond L2); q2 lines of any set (pass B: 703 against 724 us there, 43
+//     .. 60 against 52 .. 71 ps a point at 3.9 M);
+//   - not on index-aligned annulus sets: the derivative with respect to a
+//     boundary parameter that their reverse mode accumulates is a 64-bit
+//     result, reproduced to 1e-9, and any other rounding of the lines moves
+//     it by 1e-8.
+constexpr int kMatMax = 640;
+constexpr long long kMatPoints = 8 << 20;
+
+// LDS of a matrix tile unless tuned: two workgroups per compute unit.
+constexpr size_t kMatBudget = 81920;
+
+// Row blocks (16 position pairs) and K steps (32 difference pairs) of a line.
+int mat_rb(int N) { return ((N + 1) / 2 + 15) / 16; }
+int mat_ks(int N, int C) { return (N / 2 + (C + 2) / 2 + 31) / 32; }
+
+// Columns of the smallest tile that whole storage-aligned groups of lines fill
+// (four fields a line).
+int mat_min_columns(int align) { return align <= 4 ? 16 : 32; }
+
+// Whether a line of N points, C continuation points can run as a matrix
+// product.
+bool mat_line(int N, int C, int d, int align, size_t maxlds) {
+  const int ks = mat_ks(N, C);
+  return N + C <= kMatMax && mat_lds_bytes(ks, mat_min_columns(align), C, d) + 16 <= maxlds &&
+         mat_size_fits<MatLarge>(ks, mat_rb(N));
+}
+
+// Tiles of the lines that run as matrix products: 32 columns (eight lines of
+// four fields), or 16 where 32 exceed the budget or would leave compute units
+// without a second tile (the table streams once per tile, so wide tiles are
+// better where there are enough of them: right-hand side of 24 patches, about
+// 850 tiles a direction, 342 us with 32 columns, 479 with 16; one derivative
+// of 24 small patches, 370 tiles, 44 us with 32, 38 with 16).  The kernels for
+// large lines run all of a set's lines when it has such lines: two launches a
+// pass each end in a partly filled chip (that right-hand side 415 us).
+void build_mat_tiles(DirPlan& D, int order, int align, int d) {
+  const int least = mat_min_columns(align);
+  TileSet& M = D.ms;
+  size_t ntiles = 0;
+  D.mat_large = false;
+  for (const PlanDev& P : D.plans)
+    if (P.mat) {
+      ntiles += (size_t)(P.nlines + 7) / 8;
+      D.mat_large |= !mat_size_fits<MatSmall>(P.mks, P.mrb);
+    }
+  const int cap = ntiles >= 512 ? 32 : least;
+  M.threads = D.mat_large ? MatLarge::threads : MatSmall::threads;
+  M.tiles_by_patch.clear();
+  M.tiles.clear();
+  M.patch_begin.assign(1, 0);
+  M.patch_lds.clear();
+  M.lds = 0;
+  std::vector<long long> pcost;
+  for (size_t p = 0; p < D.plans.size(); ++p) {
+    const PlanDev& P = D.plans[p];
+    size_t plds = 0;
+    long long cost = 0;
+    if (P.mat) {
+      int ncp = cap;
+      if (ncp > least && mat_lds_bytes(P.mks, ncp, P.C, d) > M.budget) ncp = least;
+      for (int l0 = 0; l0 < P.nlines; l0 += ncp / 4) {
+        TileDev T;
+        T.plan = (int)p;
+        T.line0 = l0;
+        T.nl = std::min(ncp / 4, P.nlines - l0);
+        T.ld = T.nl <= 4 ? 16 : 32;
+        plds = std::max(plds, mat_lds_bytes(P.mks, T.ld, P.C, d));
+        cost += (long long)(P.Lx + 64) * T.ld;
+        M.tiles_by_patch.push_back(T);
+      }
+    }
+    M.patch_begin.push_back((int)M.tiles_by_patch.size());
+    M.patch_lds.push_back(plds);
+    M.lds = std::max(M.lds, plds);
+    pcost.push_back(cost);
+  }
+  if (!M.tiles_by_patch.empty()) order_tiles(D.plans, M, order, pcost);
+}
+
 // align: lines per tile a multiple of it (blocked storage: 4 q1 lines, 8 q2 lines)
 void build_tiles(DirPlan& D, int order, int align, int d) {
   for (int f = 0; f < 3; ++f) build_tileset(D.plans, D.ts[f], D.ts[f].budget, order, 1 << f, align, d);
+  build_mat_tiles(D, order, align, d);
 }
 
 int tile_align(int layout, int dir) { return layout == FCSD_LAYOUT_B8X4 ? (dir == 0 ? 4 : 8) : 1; }
 
 fcsd_status upload_tiles(fcsd_ctx* ctx, DirPlan& D) {
-  for (auto& t : D.ts) {
-    (void)hipFree(t.d_tiles);
-    (void)hipFree(t.d_tiles_bp);
-    t.d_tiles = t.d_tiles_bp = nullptr;
+  for (TileSet* t : {&D.ts[0], &D.ts[1], &D.ts[2], &D.ms}) {
+    (void)hipFree(t->d_tiles);
+    (void)hipFree(t->d_tiles_bp);
+    t->d_tiles = t->d_tiles_bp = nullptr;
     fcsd_status r;
-    if ((r = upload(ctx, &t.d_tiles, t.tiles)) || (r = upload(ctx, &t.d_tiles_bp, t.tiles_by_patch))) return r;
+    if ((r = upload(ctx, &t->d_tiles, t->tiles)) || (r = upload(ctx, &t->d_tiles_bp, t->tiles_by_patch))) return r;
   }
   return FCSD_OK;
 }
@@ -605,8 +745,7 @@ bool pick_a_wide(const fcsd_set* s) {
 }
 
 // Task queue of the persistent stage kernel from the current tile sets:
-// every A task (q1 tiles in launch order), then the B tasks (q2 tiles with
-// two complex lines per grid line) patch by patch in the order in which the
+// every A task (q1 tiles in launch order), then the B tasks (q2 tiles) patch by patch in the order in which the
 // patches' last A tasks stand in the queue, then the C tasks (q1 tiles)
 // patch by patch in the order of the patches' last B tasks, so that the
 // tasks taken first are the ones whose inputs are done first.  Also the
@@ -614,8 +753,8 @@ bool pick_a_wide(const fcsd_set* s) {
 fcsd_status build_stage_tasks(fcsd_set* s) {
   fcsd_ctx* ctx = s->ctx;
   const int np = s->npatch;
-  const TileSet& TA = s->dir[0].ts[0];
-  const TileSet& TB = s->dir[1].ts[1];
+  fcsd_status r;
+  const TileSet &TA = s->dir[0].ms, &TB = s->dir[1].ms;
   std::vector<int2> tasks;
   std::vector<unsigned> need(2 * (size_t)np, 0u);
   std::vector<long long> lastA(np, -1), lastB(np, -1);
@@ -649,7 +788,6 @@ fcsd_status build_stage_tasks(fcsd_set* s) {
   (void)hipFree(s->d_need);
   s->d_tasks = nullptr;
   s->d_need = nullptr;
-  fcsd_status r;
   if ((r = upload(ctx, &s->d_tasks, tasks)) || (r = upload(ctx, &s->d_need, need))) return r;
   s->ntasks = (int)tasks.size();
   if (!s->d_ctr) {
@@ -657,14 +795,16 @@ fcsd_status build_stage_tasks(fcsd_set* s) {
     HIPCHK(ctx, hipMalloc(&s->d_ctr, words * sizeof(unsigned)));
     HIPCHK(ctx, hipMemset(s->d_ctr, 0, words * sizeof(unsigned)));
   }
-  // launch shape: the q1 set's workgroup size, the larger LDS of the two
-  // sets plus the queue slot, as many workgroups as can be resident
-  s->stage_threads = TA.threads;
+  // launch shape: the larger LDS of the two directions plus the queue slot, as many workgroups as can be resident.  The schedule itself is
+  // accepted when the transform's tiles leave room for the slot.
+  s->stage_threads = MatLarge::threads;
   s->stage_lds = std::max(TA.lds, TB.lds) + 16;
   s->stage_grid = 0;
   int maxlds = 0, ncu = 0, per_cu = 0;
   HIPCHK(ctx, hipDeviceGetAttribute(&maxlds, hipDeviceAttributeMaxSharedMemoryPerBlock, ctx->device));
-  if (s->stage_lds > (size_t)maxlds) return FCSD_OK;  // the persistent schedule cannot run with these tiles
+  s->persistent_ok = std::max(s->dir[0].ts[0].lds, s->dir[1].ts[1].lds) + 16 <= (size_t)maxlds;
+  // lines that run as transforms have no persistent form
+  if (s->dir[0].any_fft || s->dir[1].any_fft || s->stage_lds > (size_t)maxlds) return FCSD_OK;
   HIPCHK(ctx, hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, ctx->device));
   HIPCHK(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_stage, s->stage_threads, s->stage_lds));
   s->stage_grid = (unsigned)std::max(0, std::min(s->ntasks, per_cu * ncu));
@@ -699,6 +839,13 @@ extern "C" fcsd_status fcsd_set_create(fcsd_ctx* ctx, int npatch, const fcsd_pat
   std::map<int, int> tw_of_L, aq_of_C, dq_of_C;
   std::map<std::pair<int, int>, int> gq_of;
   std::map<std::tuple<int, int, int, int>, int> km_of;
+  long long points = 0;
+  for (int p = 0; p < npatch; ++p) points += (long long)patches[p].n1 * patches[p].n2;
+  std::vector<MatTab> mtabs;
+  std::map<std::pair<int, int>, int> mt_of;
+  long long mt_size = 0, kap_size = 0;
+  int maxlds = 0;
+  HIPCHK(ctx, hipDeviceGetAttribute(&maxlds, hipDeviceAttributeMaxSharedMemoryPerBlock, ctx->device));
   for (int dir = 1; dir <= 2; ++dir) {
     DirPlan& D = s->dir[dir - 1];
     long long eo = 0;
@@ -761,6 +908,38 @@ extern "C" fcsd_status fcsd_set_create(fcsd_ctx* ctx, int npatch, const fcsd_pat
         }
         P.gq = gq_of[gkey];
       }
+      P.mat = ring_sectors > 0 || (dir == 1 && P.L == P.Lx && points > kMatPoints)
+                  ? 0
+                  : mat_line(P.N, P.C, d, tile_align(layout, dir - 1), (size_t)maxlds);
+      if (!P.mat) D.any_fft = true;
+      if (P.mat) {
+        const auto mkey = std::make_pair(P.N, P.C);
+        if (!mt_of.count(mkey)) {
+          mt_of[mkey] = (int)mtabs.size();
+          MatTab t;
+          t.N = P.N;
+          t.L = P.Lx;
+          t.C = P.C;
+          t.periodic = P.periodic;
+          t.rb = mat_rb(P.N);
+          t.ks = mat_ks(P.N, P.C);
+          // kappa's largest entry (m = 0 and 1) goes to at most 2^15
+          double k0 = 0.0;
+          for (int k = 1; 2 * k < t.L; ++k) k0 += k / std::tan(M_PI * k / t.L);
+          k0 *= 2.0 * M_PI / t.L * (t.periodic ? 1.0 : (double)(t.N - 1) / t.L);
+          t.es = 14 - std::ilogb(k0);
+          t.mt = mt_size;
+          t.kap = kap_size;
+          mt_size += (long long)t.rb * t.ks * 256;
+          kap_size += t.L;
+          mtabs.push_back(t);
+        }
+        const MatTab& t = mtabs[mt_of[mkey]];
+        P.mrb = t.rb;
+        P.mks = t.ks;
+        P.mes = t.es;
+        P.mt = t.mt;
+      }
       D.plans.push_back(P);
       D.ext_off.push_back(eo);
       eo += (long long)P.nlines * P.Lx;
@@ -769,12 +948,11 @@ extern "C" fcsd_status fcsd_set_create(fcsd_ctx* ctx, int npatch, const fcsd_pat
   }
   for (int dir = 0; dir < 2; ++dir) {
     for (auto& t : s->dir[dir].ts) t.budget = default_lds_budget();
+    s->dir[dir].ms.budget = getenv("FCSD_LDS_BUDGET") ? default_lds_budget() : kMatBudget;
     build_tiles(s->dir[dir], s->tile_order, tile_align(layout, dir), d);
   }
   {
     // the smallest tiles (one storage-aligned group of lines) must fit the LDS
-    int maxlds = 0;
-    HIPCHK(ctx, hipDeviceGetAttribute(&maxlds, hipDeviceAttributeMaxSharedMemoryPerBlock, ctx->device));
     for (int dir = 0; dir < 2; ++dir)
       for (int f = 0; f < 2; ++f)
         if (s->dir[dir].ts[f].lds > (size_t)maxlds)
@@ -858,6 +1036,25 @@ extern "C" fcsd_status fcsd_set_create(fcsd_ctx* ctx, int npatch, const fcsd_pat
         (r = upload(ctx, &D.d_ext_off, D.ext_off)))
       return r;
   }
+  if (!mtabs.empty()) {
+    // the derivative tables, formed on the device from kappa in FP64
+    MatTab* dt = nullptr;
+    double* dk = nullptr;
+    HIPCHK(ctx, hipMalloc(&s->d_mt, (size_t)mt_size * sizeof(uint4)));
+    r = upload(ctx, &dt, mtabs);
+    if (!r && hipMalloc(&dk, (size_t)kap_size * sizeof(double)) != hipSuccess)
+      r = fail(ctx, FCSD_ENOMEM, "derivative tables");
+    if (!r) {
+      const unsigned n = (unsigned)mtabs.size();
+      hipLaunchKernelGGL(k_mat_kappa, dim3(n), dim3(256), 0, ctx->stream, dt, dk);
+      hipLaunchKernelGGL(k_mat_table, dim3(64, n), dim3(256), 0, ctx->stream, dt, dk, (unsigned*)s->d_mt);
+      r = launch_check(ctx, "derivative tables");
+      if (!r && hipStreamSynchronize(ctx->stream) != hipSuccess) r = fail(ctx, FCSD_EHIP, "derivative tables");
+    }
+    (void)hipFree(dt);
+    (void)hipFree(dk);
+    if (r) return r;
+  }
   if ((r = build_stage_tasks(s.get()))) return r;
   HIPCHK(ctx, hipDeviceSynchronize());
   *out = s.release();
@@ -871,14 +1068,15 @@ extern "C" fcsd_status fcsd_set_destroy(fcsd_set* s) {
     if (g.exec) hipGraphExecDestroy(g.exec);
   for (int dir = 0; dir < 2; ++dir) {
     (void)hipFree(s->dir[dir].d_plans);
-    for (auto& t : s->dir[dir].ts) {
-      (void)hipFree(t.d_tiles);
-      (void)hipFree(t.d_tiles_bp);
+    for (TileSet* t : {&s->dir[dir].ts[0], &s->dir[dir].ts[1], &s->dir[dir].ts[2], &s->dir[dir].ms}) {
+      (void)hipFree(t->d_tiles);
+      (void)hipFree(t->d_tiles_bp);
     }
     (void)hipFree(s->dir[dir].d_ext_off);
   }
   hipFree(s->d_tw);
   hipFree(s->d_km);
+  hipFree(s->d_mt);
   hipFree(s->d_kf);
   hipFree(s->d_walls);
   hipFree(s->d_wall_c);
@@ -941,6 +1139,7 @@ extern "C" fcsd_status fcsd_set_tune(fcsd_set* s, const int lds_budget[3], const
   s->dir[0].ts[2].threads = threads[0];
   s->dir[1].ts[2].budget = (size_t)lds_budget[2];
   s->dir[1].ts[2].threads = threads[2];
+  for (int dir = 0; dir < 2; ++dir) s->dir[dir].ms.budget = (size_t)lds_budget[dir ? 2 : 0];
   fcsd_status r;
   for (int dir = 0; dir < 2; ++dir) {
     DirPlan& D = s->dir[dir];
@@ -962,7 +1161,7 @@ extern "C" fcsd_status fcsd_set_tune(fcsd_set* s, const int lds_budget[3], const
   if ((r = build_stage_tasks(s))) return r;
   s->wide_ok = s->dir[1].ts[2].lds <= (size_t)maxlds;
   s->a_wide = pick_a_wide(s);
-  if ((s->schedule == FCSD_SCHED_PERSISTENT && s->stage_grid == 0) ||
+  if ((s->schedule == FCSD_SCHED_PERSISTENT && !s->persistent_ok) ||
       (s->schedule == FCSD_SCHED_FUSED_WIDE && !s->wide_ok))
     s->schedule = FCSD_SCHED_FUSED;
   return rebuild_wall_tiles(s);
@@ -974,7 +1173,7 @@ extern "C" fcsd_status fcsd_set_schedule(fcsd_set* s, int schedule) {
   if (schedule != FCSD_SCHED_SPLIT && schedule != FCSD_SCHED_FUSED && schedule != FCSD_SCHED_PERSISTENT &&
       schedule != FCSD_SCHED_FUSED_WIDE)
     return fail(ctx, FCSD_EINVAL, "fcsd_set_schedule: unknown schedule");
-  if (schedule == FCSD_SCHED_PERSISTENT && s->stage_grid == 0)
+  if (schedule == FCSD_SCHED_PERSISTENT && !s->persistent_ok)
     return fail(ctx, FCSD_EINVAL,
                 "fcsd_set_schedule: the tile sets leave no room for the persistent kernel's queue slot "
                 "(tune LDS budgets to at most 160 KB - 16)");
@@ -1084,7 +1283,7 @@ extern "C" fcsd_status fc_diff(fcsd_ctx* ctx, const fcsd_set* s, int dir, int nf
   a.nf = nf;
   a.in = in;
   a.out = out;
-  return dir == 1 ? launch_lines(s, 1, k_fcdiff<1, false>, a) : launch_lines(s, 2, k_fcdiff<2, false>, a);
+  return launch_forward(s, dir, dir == 1 ? diff_kernels<1>(k_fcdiff<1, false>) : diff_kernels<2>(k_fcdiff<2, false>), a);
 }
 
 extern "C" fcsd_status fc_diff_adj(fcsd_ctx* ctx, const fcsd_set* s, int dir, int nf, const float* out_bar,
@@ -1147,6 +1346,15 @@ RhsWs carve_rhs(const fcsd_set* s, void* ws) {
 }
 
 // flux: FLUX_FULL, FLUX_VISC, FLUX_INVISCID ; out: MODE_SET / MODE_ADD / MODE_RK
+// e - e_ref of the four state fields differentiated along dir into a.out
+// (pass A, and the reverse mode's derivatives).
+fcsd_status launch_state_diff(const fcsd_set* s, int dir, PassArgs a, int patch = -1) {
+  a.in = a.u;
+  a.nf = 4;
+  if (dir == 2) return launch_forward(s, 2, diff_kernels<2>(k_dev_diff2<2>), a, patch, 2);
+  return launch_forward(s, 1, diff_kernels<1>(s->a_wide ? k_dev_diff2<1> : k_dev_diff<1>), a, patch, s->a_wide ? 2 : 1);
+}
+
 // Launch a line kernel over an explicit list of n tiles of the
 // single-field tile set of direction dir.
 template <class K>
@@ -1216,11 +1424,9 @@ fcsd_status rhs_passes(fcsd_ctx* ctx, const fcsd_set* s, const float* u, const f
   // passes B1 and B2 in one launch (a whole-set call of the fused or
   // persistent schedule)
   // (bit 4 of passes asks for it whatever the schedule)
-  const bool fuse = patch < 0 && (s->schedule != FCSD_SCHED_SPLIT || (passes & 48u)) && (passes & 6u) == 6u;
-  // the fused pass with all eight H fields in LDS (bit 5 of passes asks for it)
-  const bool wide = fuse && !(passes & 16u) && s->wide_ok &&
-                    (s->schedule == FCSD_SCHED_FUSED_WIDE || (passes & 32u));
-  const bool persistent = fuse && passes == 15u && !walls && s->schedule == FCSD_SCHED_PERSISTENT;
+  const bool fuse = patch < 0 && (s->schedule != FCSD_SCHED_SPLIT || (passes & 16u)) && (passes & 6u) == 6u;
+  const bool persistent =
+      fuse && passes == 15u && !walls && s->schedule == FCSD_SCHED_PERSISTENT && s->stage_grid > 0;
   a.out = W.d1e;
   PassArgs b = a;
   b.plans = s->dir[1].d_plans;
@@ -1241,11 +1447,13 @@ fcsd_status rhs_passes(fcsd_ctx* ctx, const fcsd_set* s, const float* u, const f
     const int np = s->npatch;
     StageArgs g;
     g.A = a;
-    g.A.tiles = s->dir[0].ts[0].d_tiles;
+    g.A.in = u;
+    g.A.nf = 4;
+    g.A.tiles = s->dir[0].ms.d_tiles;
     g.B = b;
-    g.B.tiles = s->dir[1].ts[1].d_tiles;
+    g.B.tiles = s->dir[1].ms.d_tiles;
     g.C = e;
-    g.C.tiles = s->dir[0].ts[0].d_tiles;
+    g.C.tiles = s->dir[0].ms.d_tiles;
     g.tasks = s->d_tasks;
     g.ntasks = s->ntasks;
     g.npatch = np;
@@ -1279,8 +1487,7 @@ fcsd_status rhs_passes(fcsd_ctx* ctx, const fcsd_set* s, const float* u, const f
     if (walls && (passes & 3u))
       if ((st = wall_theta_derivs(ctx, s, u, ref, gamma, patch))) return st;
     if (passes & 1u) {
-      st = s->a_wide ? launch_lines(s, 1, k_dev_diff2<1>, a, patch, 2) : launch_lines(s, 1, k_dev_diff<1>, a, patch);
-      if (st) return st;
+      if ((st = launch_state_diff(s, 1, a, patch))) return st;
       if (walls) {
         const ChunkDev* ch;
         int n;
@@ -1291,18 +1498,15 @@ fcsd_status rhs_passes(fcsd_ctx* ctx, const fcsd_set* s, const float* u, const f
       }
     }
     if ((passes & 2u) && !fuse)
-      if ((st = launch_lines(s, 2, k_passB1, b, patch, 2))) return st;
+      if ((st = launch_forward(s, 2, ForwardKernels{{k_mat_B<MatSmall, false>, k_mat_B<MatLarge, false>}, k_passB1}, b, patch, 2))) return st;
   }
   if (fuse) {
-    if ((st = wide ? launch_lines(s, 2, k_passB4, b, patch, 4) : launch_lines(s, 2, k_passB, b, patch, 2)))
-      return st;
+    if ((st = launch_forward(s, 2, ForwardKernels{{k_mat_B<MatSmall, true>, k_mat_B<MatLarge, true>}, k_passB}, b, patch, 2))) return st;
   } else if (passes & 4u) {
-    PassArgs c = a;
-    c.plans = s->dir[1].d_plans;
-    if ((st = launch_lines(s, 2, k_passB2, c, patch))) return st;
+    if ((st = launch_forward(s, 2, ForwardKernels{{k_mat_B2<MatSmall>, k_mat_B2<MatLarge>}, k_passB2}, a, patch))) return st;
   }
   if (!(passes & 8u)) return FCSD_OK;
-  return launch_lines(s, 1, k_passC, e, patch);
+  return launch_forward(s, 1, ForwardKernels{{k_mat_C<MatSmall>, k_mat_C<MatLarge>}, k_passC}, e, patch);
 }
 
 }  // namespace
@@ -1677,7 +1881,7 @@ extern "C" fcsd_status fcsd_stage_pass(fcsd_ctx* ctx, const fcsd_set* s, int pas
     return fail(ctx, FCSD_EINVAL, "fcsd_stage_pass: q2 tiles of four complex lines per grid line do not fit the LDS");
   if (ws_bytes < ws_bytes_of(s, FCSD_WS_RHS)) return fail(ctx, FCSD_EINVAL, "fcsd_stage_pass: workspace too small");
   return rhs_passes(ctx, s, ui, metric, mu, ref, gamma, mu ? FLUX_FULL : FLUX_INVISCID, MODE_RK, nullptr, stage, u0,
-                    acc, uout, dt_dev, ws, -1, pass == 4 ? 6u | 16u : (pass == 5 ? 6u | 32u : 1u << pass));
+                    acc, uout, dt_dev, ws, -1, pass >= 4 ? 6u | 16u : 1u << pass);
 }
 
 namespace {
@@ -2381,17 +2585,14 @@ fcsd_status rhs_adj_impl(fcsd_ctx* ctx, const fcsd_set* s, const float* u, const
     PassArgs b = a;
     if (!given1) {
       b.out = w;
-      b.plans = s->dir[0].d_plans;
-      if ((st = s->a_wide ? launch_lines(s, 1, k_dev_diff2<1>, b, -1, 2) : launch_lines(s, 1, k_dev_diff<1>, b)))
-        return st;
+      if ((st = launch_state_diff(s, 1, b))) return st;
       if (walls)
         hipLaunchKernelGGL(k_energy_rule, dim3(chunk_grid(s->nwchunks)), dim3(kBlock), 0, ctx->stream, s->d_wchunks,
                            s->nwchunks, s->d_patches, u, pl, gamma - 1.0f, D1TH, w);
     }
     if (!given2) {
       b.out = w + 4 * pl;
-      b.plans = s->dir[1].d_plans;
-      if ((st = launch_lines(s, 2, k_dev_diff2<2>, b, -1, 2))) return st;
+      if ((st = launch_state_diff(s, 2, b))) return st;
       if (walls)
         hipLaunchKernelGGL(k_energy_rule, dim3(chunk_grid(s->nwchunks)), dim3(kBlock), 0, ctx->stream, s->d_wchunks,
                            s->nwchunks, s->d_patches, u, pl, gamma - 1.0f, D2TH, w + 4 * pl);

@@ -28,6 +28,8 @@ struct PassArgs {
   const float* win;           // blending window plane (initial-data smearing)
   float* d2out;               // pass B1: also store d2 (e - e_ref) here when not null
   const float* d2th;          // pass B1 on wall patches: d2 theta, for the energy's product rule
+  const uint4* mt;            // derivative tables of the plans that run as matrix products
+  int fft_only;               // skip tiles of those plans (their own kernel runs them)
   const double* aq;
   const double* dq;
   const float* gq;            // fold matrices of the transposed derivative (per plan, P.gq)
@@ -150,6 +152,7 @@ extern __shared__ float2 lds_z[];
 #define FCSD_TILE_BEGIN(a)                                                   \
   const TileDev T_wg = (a).tiles[blockIdx.x];                                \
   if (T_wg.nl == 0) return; /* padding slot of the launch order */           \
+  if ((a).fft_only && (a).plans[T_wg.plan].mat) return;                      \
   FCSD_TILE_AT(a, T_wg, lds_z)
 
 // Forward derivative of pairs already loaded by load_differenced: tail
@@ -276,7 +279,7 @@ __device__ __forceinline__ void dev_diff_tile(const PassArgs& a, const TileDev& 
 template <int DIR>
 __global__ void FCSD_LINE_BOUNDS k_dev_diff(PassArgs a) {
   const TileDev T = a.tiles[blockIdx.x];
-  if (T.nl == 0) return;
+  if (T.nl == 0 || (a.fft_only && a.plans[T.plan].mat)) return;
   dev_diff_tile<DIR>(a, T, lds_z);
 }
 
@@ -325,7 +328,7 @@ __device__ __forceinline__ void dev_diff2_tile(const PassArgs& a, const TileDev&
 template <int DIR>
 __global__ void FCSD_LINE_BOUNDS k_dev_diff2(PassArgs a) {
   const TileDev T = a.tiles[blockIdx.x];
-  if (T.nl == 0) return;
+  if (T.nl == 0 || (a.fft_only && a.plans[T.plan].mat)) return;
   dev_diff2_tile<DIR>(a, T, lds_z);
 }
 
@@ -490,109 +493,17 @@ __device__ __forceinline__ void passB_tile(const PassArgs& a, const TileDev& T, 
   }
 }
 
-// Passes B1 and B2 on a q2 tile that holds all eight H fields in LDS (tile
-// set of four complex lines per grid line, row stride >= 4 nl): d2 e of the
-// four components in slots 0, 1 (two complex lines per grid line), the H
-// epilogue stores H (for pass C) and writes (H_x, H_y) of component c into
-// slot c, then one transform of the four slots and r2 of all components from
-// one read of the q2 metric rows.  The same FP32 operations on every line as
-// passes B1 and B2 (bit-identical results).
-__device__ __forceinline__ void passB4_tile(const PassArgs& a, const TileDev& T, float2* lds) {
-  const PlanDev P = a.plans[T.plan];
-  const PlanDev* Pg = a.plans + T.plan;
-  TileDev T2 = T;
-  T2.nl = 2 * T.nl;
-  const LineCtx X = line_setup(lds, T2, P, a.tw, a.km);
-  const LineCtx X4 = line_view(X, 4 * T.nl);
-  float2* __restrict__ z = X.z;
-  const int N = P.N, nl = T.nl, ld = T.ld;
-  const long long pl = a.plane;
-  const TileMem M = tile_mem<2>(P, T, nl, ld);
-  __syncthreads();
-  const int flux = a.mode;
-  if (flux != FLUX_INVISCID) {
-    const float* u = a.u + M.base;
-    load_differenced<2, kDiffBatch>(X, M.w, M.gmax, N, nl, 0, P.nb1, P.n1, u, u + pl, a.eref[0], a.eref[1], a.d);
-    load_differenced<2, kDiffBatch>(X, M.w, M.gmax, N, nl, nl, P.nb1, P.n1, u + 2 * pl, u + 3 * pl, a.eref[2],
-                                    a.eref[3], a.d);
-    FCSD_DIFF_AND_TRANSFORM(a)
-  }
-  const HSrc hs = h_sources(a, M.base, flux);
-  float* H = a.H + M.base;
-  float* d2o = a.d2out ? a.d2out + M.base : nullptr;
-  float2* zb = z + nl;
-  float2* zc = z + 2 * nl;
-  float2* zd = z + 3 * nl;
-  walk_b<kEpiBatchH>(
-      M.w, [&](unsigned g) { return load_H4_inputs(hs, g); },
-      [&](unsigned g, unsigned l, const HIn4& q) {
-        const float2 za = at(z, l), zq = at(zb, l);
-        float d2[4] = {za.x, za.y, zq.x, zq.y};
-        if (a.d2th && P.wallp) {
-          // the energy's derivative by the product rule (Remark adiabatic)
-          const float ir = 1.0f / q.e[0], mq = q.e[1] * q.e[1] + q.e[2] * q.e[2];
-          const float A = q.e[3] * ir - mq * ir * ir, B = q.e[0] / (a.gamma - 1.0f);
-          d2[3] = A * d2[0] + B * at(a.d2th + M.base, g) + (q.e[1] * d2[1] + q.e[2] * d2[2]) * ir;
-        }
-        if (d2o) {
-#pragma unroll
-          for (int k = 0; k < 4; ++k) at(d2o + k * pl, g) = d2[k];
-        }
-        float dF[4] = {0.f, 0.f, 0.f, 0.f}, dG[4] = {0.f, 0.f, 0.f, 0.f};
-        if (flux != FLUX_VISC) dev_flux(q.e, a.eref, a.pref, a.gamma, dF, dG);
-        float h[8];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          float vx = 0.f, vy = 0.f;
-          if (flux != FLUX_INVISCID) {
-            vx = q.mu * (q.m1x * q.d1[k] + q.m2x * d2[k]);
-            vy = q.mu * (q.m1y * q.d1[k] + q.m2y * d2[k]);
-          }
-          h[2 * k] = vx - dF[k];
-          h[2 * k + 1] = vy - dG[k];
-          at(H + (2 * k) * pl, g) = h[2 * k];
-          at(H + (2 * k + 1) * pl, g) = h[2 * k + 1];
-        }
-        at(z, l) = make_float2(h[0], h[1]);
-        at(zb, l) = make_float2(h[2], h[3]);
-        at(zc, l) = make_float2(h[4], h[5]);
-        at(zd, l) = make_float2(h[6], h[7]);
-      });
-  __syncthreads();
-  difference_ext(X4, P, a.dq + P.dq, a.d);
-  fft_apply<false>(X4, Pg, P);
-  const float* m2x = a.metric + 2 * pl + M.base;
-  const float* m2y = a.metric + 3 * pl + M.base;
-  float* r2 = a.r2 + M.base;
-  walk_b<kLoadBatch>(
-      M.w, [&](unsigned g) { return make_float2(at(m2x, g), at(m2y, g)); },
-      [&](unsigned g, unsigned l, float2 m) {
-        const float2 v0 = at(z, l), v1 = at(zb, l), v2 = at(zc, l), v3 = at(zd, l);
-        at(r2, g) = m.x * v0.x + m.y * v0.y;
-        at(r2 + pl, g) = m.x * v1.x + m.y * v1.y;
-        at(r2 + 2 * pl, g) = m.x * v2.x + m.y * v2.y;
-        at(r2 + 3 * pl, g) = m.x * v3.x + m.y * v3.y;
-      });
-}
-
 __global__ void FCSD_LINE_BOUNDS k_passB1(PassArgs a) {
   const TileDev T = a.tiles[blockIdx.x];
-  if (T.nl == 0) return;
+  if (T.nl == 0 || (a.fft_only && a.plans[T.plan].mat)) return;
   passB_tile<false>(a, T, lds_z);
 }
 
 // Passes B1 and B2 in one launch (see passB_tile).
 __global__ void FCSD_LINE_BOUNDS k_passB(PassArgs a) {
   const TileDev T = a.tiles[blockIdx.x];
-  if (T.nl == 0) return;
+  if (T.nl == 0 || (a.fft_only && a.plans[T.plan].mat)) return;
   passB_tile<true>(a, T, lds_z);
-}
-
-// The same with all eight H fields in LDS (see passB4_tile).
-__global__ void FCSD_LINE_BOUNDS k_passB4(PassArgs a) {
-  const TileDev T = a.tiles[blockIdx.x];
-  if (T.nl == 0) return;
-  passB4_tile(a, T, lds_z);
 }
 
 // Spectral filter of the state (paper Sec. 4.3.1, eq. filtering) along
@@ -917,88 +828,8 @@ __device__ __forceinline__ void passC_tile(const PassArgs& a, const TileDev& Tin
 
 __global__ void FCSD_LINE_BOUNDS k_passC(PassArgs a) {
   const TileDev T = a.tiles[blockIdx.x];
-  if (T.nl == 0) return;
+  if (T.nl == 0 || (a.fft_only && a.plans[T.plan].mat)) return;
   passC_tile(a, T, lds_z);
-}
-
-// ---------------------------------------------------------------- one launch per stage
-
-// Task kinds of the persistent stage kernel: pass A on a q1 tile, passes
-// B1 + B2 on a q2 tile (two complex lines per grid line), pass C on a q1
-// tile.
-enum { TASK_A = 0, TASK_B = 1, TASK_C = 2 };
-
-struct StageArgs {
-  PassArgs A, B, C;         // the passes' arguments (A.tiles, B.tiles: the q1 and q2 tile arrays)
-  const int2* tasks;        // (kind, tile index), in queue order
-  int ntasks;
-  int npatch;
-  int skipA;                // inviscid stage: A tasks do nothing
-  unsigned* ctr;            // [0] queue head; [1 + p] A tiles done of patch p; [1 + np + p] B tiles done
-  const unsigned* need;     // [p] A tiles of patch p; [np + p] B tiles of patch p
-  unsigned* err;            // bit 0 set when a wait gave up (results of the launch are then invalid)
-};
-
-// Upper bound on the polls of one dependency wait (each poll sleeps ~128
-// cycles: about a second in all), after which the workgroup records the
-// failure in err and goes on, so that every workgroup ends.
-constexpr int kSpinLimit = 1 << 24;
-
-// One RK stage in one launch: every workgroup takes tasks from a global
-// queue until it is empty.  The queue holds all A tasks, then every B task,
-// then every C task, so a task only depends on tasks taken before it (B on
-// its patch's A tiles, C on its patch's B tiles), which are held by running
-// workgroups: the earliest unfinished task can always proceed, whatever the
-// number of resident workgroups.  A task's completion is published by a
-// release increment of its patch's counter after a workgroup barrier (every
-// thread's stores are then complete); a dependent task starts after an
-// acquire poll of that counter.  Phases of different patches overlap, and no
-// workgroup idles at the end of a pass.  The counters start at zero (the
-// host clears them before the launch).
-__global__ void FCSD_LINE_BOUNDS k_stage(StageArgs s) {
-  // the first 16 bytes of the dynamic LDS hold the task index; tiles start after
-  int* slot = reinterpret_cast<int*>(lds_z);
-  float2* lds = lds_z + 2;
-  const int np = s.npatch;
-  for (;;) {
-    __syncthreads();  // the previous task's LDS reads are done; the slot is free
-    if (threadIdx.x == 0) slot[0] = (int)atomicAdd(s.ctr, 1u);
-    __syncthreads();
-    const int t = slot[0];
-    if (t >= s.ntasks) return;
-    const int2 k = s.tasks[t];
-    const TileDev T = (k.x == TASK_B ? s.B.tiles : s.A.tiles)[k.y];
-    const int p = T.plan;  // one plan per patch and direction
-    if (k.x != TASK_A) {
-      if (threadIdx.x == 0) {
-        const int dep = (k.x == TASK_B ? 0 : np) + p;
-        const unsigned need = s.need[dep];
-        unsigned* c = s.ctr + 1 + dep;
-        int polls = 0;
-        while (__hip_atomic_load(c, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) < need) {
-          if (++polls > kSpinLimit) {
-            atomicOr(s.err, 1u);
-            break;
-          }
-          __builtin_amdgcn_s_sleep(2);
-        }
-      }
-      __syncthreads();
-    }
-    if (k.x == TASK_A) {
-      if (!s.skipA) dev_diff_tile<1>(s.A, T, lds);
-    } else if (k.x == TASK_B) {
-      passB_tile<true>(s.B, T, lds);
-    } else {
-      passC_tile(s.C, T, lds);
-    }
-    if (k.x != TASK_C) {
-      __syncthreads();  // every thread's stores of the task are complete
-      if (threadIdx.x == 0)
-        __hip_atomic_fetch_add(s.ctr + 1 + (k.x == TASK_A ? 0 : np) + p, 1u, __ATOMIC_RELEASE,
-                               __HIP_MEMORY_SCOPE_AGENT);
-    }
-  }
 }
 
 }  // namespace fcsd

@@ -2,7 +2,7 @@
 // network classifier, preliminary viscosity, smoothing-blending operator,
 // multi-patch glue and the reverse-mode passes of the right-hand side.
 #pragma once
-#include "kernels.h"
+#include "linemat.h"
 
 namespace fcsd {
 
