@@ -12,6 +12,7 @@
 #include <map>
 #include <memory>
 #include <mutex>
+#include <queue>
 #include <string>
 #include <tuple>
 #include <vector>
@@ -99,11 +100,13 @@ struct TileSet {
   size_t lds = 0;
   TileDev* d_tiles = nullptr;
   TileDev* d_tiles_bp = nullptr;
+  double estimate = 0.0;                  // of a forward pass over it (pick_forward_tiles); 0: tuned
 };
 
 struct DirPlan {
   std::vector<PlanDev> plans;             // one per patch
   TileSet ts[3];                          // one / two / four complex lines per grid line
+  TileSet fs[2];                          // the forward passes' tiles: one / two complex lines per grid line
   TileSet ms;                             // lines whose derivative runs as a matrix product (linemat.h)
   bool mat_large = false;                 // by the kernels for large lines
   bool any_fft = false;                   // lines that run as transforms
@@ -247,10 +250,10 @@ void set_ref(PassArgs& a, const float ref[4], float gamma) {
 unsigned blocks_for(long long n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 unsigned chunk_grid(int nchunks) { return (unsigned)std::max(1, std::min(nchunks, kChunkGrid)); }
 
-// launch a line-engine kernel over the batched tile list or one patch's tiles
+// launch a line-engine kernel over a tile set, the batched list or one patch's
+// tiles
 template <class K>
-fcsd_status launch_lines(const fcsd_set* s, int dir, K kern, PassArgs a, int patch = -1, int fields = 1) {
-  const TileSet& D = s->dir[dir - 1].ts[fields == 4 ? 2 : fields - 1];
+fcsd_status launch_tileset(const fcsd_set* s, const TileSet& D, K kern, PassArgs a, int patch = -1) {
   unsigned grid;
   size_t lds;
   if (patch < 0) {
@@ -265,6 +268,12 @@ fcsd_status launch_lines(const fcsd_set* s, int dir, K kern, PassArgs a, int pat
   if (grid == 0) return FCSD_OK;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(D.threads), lds, s->ctx->stream, a);
   return launch_check(s->ctx, "line kernel");
+}
+
+// the same over the tiles of `fields` complex lines per grid line
+template <class K>
+fcsd_status launch_lines(const fcsd_set* s, int dir, K kern, PassArgs a, int patch = -1, int fields = 1) {
+  return launch_tileset(s, s->dir[dir - 1].ts[fields == 4 ? 2 : fields - 1], kern, a, patch);
 }
 
 // A forward line pass as kernels: of lines that run as matrix products (small
@@ -301,7 +310,7 @@ fcsd_status launch_forward(const fcsd_set* s, int dir, const ForwardKernels& K, 
   }
   if (patch < 0 ? !D.any_fft : D.plans[patch].mat != 0) return FCSD_OK;
   a.fft_only = 1;
-  return launch_lines(s, dir, K.fft, a, patch, fields);
+  return launch_tileset(s, D.fs[fields - 1], K.fft, a, patch);
 }
 
 fcsd_status check_set(fcsd_ctx* ctx, const fcsd_set* s, int64_t plane) {
@@ -563,6 +572,7 @@ void order_tiles(const std::vector<PlanDev>& plans, TileSet& D, int order, const
     for (size_t k = 0; k < lst[x].size(); ++k) D.tiles[k * kXcd + x] = lst[x][k];
 }
 
+// (order < 0: the tiles only, not the launch order.)
 void build_tileset(const std::vector<PlanDev>& plans, TileSet& D, size_t budget, int order, int fields, int align,
                    int d) {
   D.tiles_by_patch.clear();
@@ -604,7 +614,71 @@ void build_tileset(const std::vector<PlanDev>& plans, TileSet& D, size_t budget,
     D.lds = std::max(D.lds, plds);
     pcost.push_back(cost);
   }
-  order_tiles(plans, D, order, pcost);
+  if (order >= 0) order_tiles(plans, D, order, pcost);
+}
+
+// Estimate of a transform pass over a tile set, in samples of complex lines at
+// the rate of a full compute unit (about 500 a microsecond): every tile takes a
+// fixed kFixed samples' time (its phases' latency) plus its samples, shared
+// with the other workgroups of its compute unit; the tiles fill the
+// 256 x per_cu places in turn.
+constexpr double kFixed = 3000.0;
+double pass_estimate(const std::vector<PlanDev>& plans, const TileSet& D, int fields, int per_cu) {
+  const size_t n = D.tiles_by_patch.size();
+  const int r = (int)std::max<size_t>(1, std::min<size_t>(per_cu, (n + 255) / 256));
+  const size_t places = 256 * (size_t)r;
+  std::vector<double> t(n);
+  double sum = 0.0;
+  for (size_t i = 0; i < n; ++i) {
+    const TileDev& T = D.tiles_by_patch[i];
+    t[i] = kFixed + (double)r * plans[T.plan].L * T.nl * fields;
+    sum += t[i];
+  }
+  if (n > 8 * places) return sum / places;
+  std::sort(t.begin(), t.end(), std::greater<double>());
+  std::priority_queue<double, std::vector<double>, std::greater<double>> q;
+  double end = 0.0;
+  for (double v : t) {
+    double at = 0.0;
+    if (q.size() == places) {
+      at = q.top();
+      q.pop();
+    }
+    q.push(at + v);
+    end = std::max(end, at + v);
+  }
+  return end;
+}
+
+// Tile split of the forward transform passes of an untuned set: the LDS budget
+// whose estimate is least, workgroups of 512 threads (two per compute unit),
+// or the whole LDS with 1024.  A budget of 64 KB and 256 threads leaves a small
+// set with fewer workgroups than compute units, and a larger one with a last,
+// nearly empty round of them: steps of annuli of 16 x 64 x 64, 16 x 128 x 128,
+// 128 x 101 x 101 and 64 x 256 x 256 points take 817, 1004, 1227 and 3516 us
+// with it, 447, 563, 860 and 2434 at their best of 36 splits.  Results do not
+// depend on the split.  (The reverse passes, whose folds sum in an order that
+// depends on it, keep theirs.)
+void pick_forward_tiles(DirPlan& D, int f, int order, int align, int d, size_t maxlds) {
+  TileSet& F = D.fs[f];
+  double best = 0.0;
+  size_t budget = 0;
+  for (size_t kb : {8, 10, 12, 14, 16, 20, 24, 28, 32, 40, 48, 56, 64, 72, 80, 160}) {
+    const size_t b = std::min(kb * 1024, maxlds);
+    TileSet t;
+    build_tileset(D.plans, t, b, -1, 1 << f, align, d);
+    if (t.lds > maxlds || (kb < 160 && t.lds > 81920)) continue;
+    const double e = pass_estimate(D.plans, t, 1 << f, kb < 160 ? 2 : 1);
+    if (budget == 0 || e < best) {
+      best = e;
+      budget = b;
+      F.threads = kb < 160 ? 512 : 1024;
+    }
+  }
+  F.budget = budget ? budget : maxlds;
+  if (!budget) F.threads = 1024;
+  build_tileset(D.plans, F, F.budget, order, 1 << f, align, d);
+  F.estimate = best;
 }
 
 // Lines whose derivative runs as a matrix product (linemat.h), a rule on the
@@ -697,16 +771,28 @@ void build_mat_tiles(DirPlan& D, int order, int align, int d) {
   if (!M.tiles_by_patch.empty()) order_tiles(D.plans, M, order, pcost);
 }
 
-// align: lines per tile a multiple of it (blocked storage: 4 q1 lines, 8 q2 lines)
-void build_tiles(DirPlan& D, int order, int align, int d) {
+// align: lines per tile a multiple of it (blocked storage: 4 q1 lines, 8 q2
+// lines); maxlds > 0: the forward passes' split is picked for the set
+// (untuned), else it is that of ts.
+void build_tiles(DirPlan& D, int order, int align, int d, size_t maxlds = 0) {
   for (int f = 0; f < 3; ++f) build_tileset(D.plans, D.ts[f], D.ts[f].budget, order, 1 << f, align, d);
+  for (int f = 0; f < 2; ++f) {
+    if (maxlds) {
+      pick_forward_tiles(D, f, order, align, d, maxlds);
+    } else {
+      D.fs[f].budget = D.ts[f].budget;
+      D.fs[f].threads = D.ts[f].threads;
+      D.fs[f].estimate = 0.0;
+      build_tileset(D.plans, D.fs[f], D.fs[f].budget, order, 1 << f, align, d);
+    }
+  }
   build_mat_tiles(D, order, align, d);
 }
 
 int tile_align(int layout, int dir) { return layout == FCSD_LAYOUT_B8X4 ? (dir == 0 ? 4 : 8) : 1; }
 
 fcsd_status upload_tiles(fcsd_ctx* ctx, DirPlan& D) {
-  for (TileSet* t : {&D.ts[0], &D.ts[1], &D.ts[2], &D.ms}) {
+  for (TileSet* t : {&D.ts[0], &D.ts[1], &D.ts[2], &D.fs[0], &D.fs[1], &D.ms}) {
     (void)hipFree(t->d_tiles);
     (void)hipFree(t->d_tiles_bp);
     t->d_tiles = t->d_tiles_bp = nullptr;
@@ -736,11 +822,13 @@ void filter_table(const PlanDev& P, double alpha, int p, std::vector<float>& t) 
 unsigned* set_error_word(const fcsd_set* s) { return s->d_ctr + 1 + 2 * (size_t)s->npatch; }
 
 // Pass A runs on the q1 tiles of two complex lines per grid line (the four
-// state fields in one round) when those tiles keep within the q1 tiles' LDS
-// (a launch takes its largest tile's LDS; long lines, whose two-line tiles
+// state fields in one round) when that is estimated faster than two rounds on
+// the one-line tiles; on tuned sets when those tiles keep within the q1 tiles'
+// LDS (a launch takes its largest tile's LDS; long lines, whose two-line tiles
 // need more, would halve the workgroups per CU for the whole pass).
 bool pick_a_wide(const fcsd_set* s) {
-  const TileSet &one = s->dir[0].ts[0], &two = s->dir[0].ts[1];
+  const TileSet &one = s->dir[0].fs[0], &two = s->dir[0].fs[1];
+  if (one.estimate > 0.0 && two.estimate > 0.0) return two.estimate <= 2.0 * one.estimate;
   return two.lds <= std::max(one.lds, one.budget);
 }
 
@@ -949,7 +1037,9 @@ extern "C" fcsd_status fcsd_set_create(fcsd_ctx* ctx, int npatch, const fcsd_pat
   for (int dir = 0; dir < 2; ++dir) {
     for (auto& t : s->dir[dir].ts) t.budget = default_lds_budget();
     s->dir[dir].ms.budget = getenv("FCSD_LDS_BUDGET") ? default_lds_budget() : kMatBudget;
-    build_tiles(s->dir[dir], s->tile_order, tile_align(layout, dir), d);
+    // (a budget asked for by the environment counts as tuning)
+    build_tiles(s->dir[dir], s->tile_order, tile_align(layout, dir), d,
+                getenv("FCSD_LDS_BUDGET") ? 0 : (size_t)maxlds);
   }
   {
     // the smallest tiles (one storage-aligned group of lines) must fit the LDS
@@ -1068,7 +1158,8 @@ extern "C" fcsd_status fcsd_set_destroy(fcsd_set* s) {
     if (g.exec) hipGraphExecDestroy(g.exec);
   for (int dir = 0; dir < 2; ++dir) {
     (void)hipFree(s->dir[dir].d_plans);
-    for (TileSet* t : {&s->dir[dir].ts[0], &s->dir[dir].ts[1], &s->dir[dir].ts[2], &s->dir[dir].ms}) {
+    for (TileSet* t : {&s->dir[dir].ts[0], &s->dir[dir].ts[1], &s->dir[dir].ts[2], &s->dir[dir].fs[0],
+                       &s->dir[dir].fs[1], &s->dir[dir].ms}) {
       (void)hipFree(t->d_tiles);
       (void)hipFree(t->d_tiles_bp);
     }
@@ -1892,12 +1983,12 @@ fcsd_status filter_impl(fcsd_ctx* ctx, const fcsd_set* s, const float* in, float
   a.gamma = gamma;
   a.in = in;
   a.out = out;
-  fcsd_status st = launch_lines(s, 1, k_filter<1>, a, -1, 2);
+  fcsd_status st = launch_tileset(s, s->dir[0].fs[1], k_filter<1>, a);
   if (st) return st;
   PassArgs b = a;
   b.plans = s->dir[1].d_plans;
   b.in = out;
-  return launch_lines(s, 2, k_filter<2>, b, -1, 2);
+  return launch_tileset(s, s->dir[1].fs[1], k_filter<2>, b);
 }
 
 // Reverse mode of filter_impl at state e: out_bar (cotangent of the

@@ -1,0 +1,58 @@
+"""The forward passes' tile split that an untuned set picks for itself changes no
+bit: derivatives, right-hand side and filter of untuned sets equal those of the
+same sets tuned to other splits."""
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2506_16076_amd import api
+    ctx = api.Context(0)
+    yield api, ctx, torch
+    ctx.sync()
+
+
+CASES = {
+    "one small patch": lambda: synth.config(0, n=48),
+    "few short lines": lambda: synth.config(3, n=48),
+    "uneven": lambda: synth.config(2, npatch=9, nmax=200),
+    "many patches, d = 2": lambda: synth.paper_subpatches(16, 4),
+    "long lines": lambda: synth.config(0, n=700),
+}
+
+
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("name", list(CASES))
+def test_untuned_split_changes_no_bit(env, name, layout):
+    api, ctx, torch = env
+    cfg = CASES[name]()
+    ps = cfg.ps
+    if name == "long lines":
+        ps = synth.unit_square(700, C=28)      # 728 = 2^3 7 13
+        cfg.u0 = synth._f32(synth.square_state(ps, np.random.default_rng(0)), ps)
+    outs = []
+    for tune in (None, (163840, 1024), (24576, 256)):
+        s = api.PatchSet.from_layout(ctx, ps, layout)
+        if tune:
+            s.tune(*tune)
+        s.set_filter(10.0, 14)
+        u, metric = s.to_device(cfg.u0), s.to_device(ps.metric)
+        mu = s.to_device(np.full((1, ps.plane), 1e-3, np.float32))
+        rhs, d1, d2, uf = (torch.zeros_like(u) for _ in range(4))
+        api.fcsd_rhs(s, u, metric, mu, cfg.ref, 1.4, rhs)
+        api.fc_diff(s, 1, u, d1, 4)
+        api.fc_diff(s, 2, u, d2, 4)
+        api.fcsd_filter(s, u, uf, 1.4)
+        outs.append([s.to_host(t) for t in (rhs, d1, d2, uf)])
+        s.close()
+    for o in outs[1:]:
+        for a, b in zip(o, outs[0]):
+            assert np.array_equal(a, b)
