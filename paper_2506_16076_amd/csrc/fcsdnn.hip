@@ -1668,7 +1668,7 @@ fcsd_status cfl_dt_impl(fcsd_ctx* ctx, const fcsd_set* s, const float* u, const 
   unsigned* mmax = red + np;
   hipLaunchKernelGGL(k_fill, dim3(blocks_for(2 * np)), dim3(kBlock), 0, ctx->stream, (float*)red, 0.f,
                      (long long)(2 * np));
-  hipLaunchKernelGGL(k_dt_reduce, dim3(chunk_grid(s->nchunks)), dim3(kBlock), 0, ctx->stream, s->d_chunks, s->nchunks, s->d_patches, u, mu,
+  hipLaunchKernelGGL(k_dt_reduce, dim3(dt_grid(s->nchunks)), dim3(kBlock), 0, ctx->stream, s->d_chunks, s->nchunks, s->d_patches, u, mu,
                      (long long)s->plane, gamma, smax, mmax);
   hipLaunchKernelGGL(k_dt_final, dim3(1), dim3(kBlock), 0, ctx->stream, s->d_patches, np, smax, mmax, cfl, dt_dev);
   return launch_check(ctx, "cfl_dt");
