@@ -62,11 +62,21 @@ struct PlanDev {
   long long off; // patch offset in a plane
 };
 
+// How many lanes share a line in the transposed operators' fold (fold_pre):
+// what a tile of n grid lines gives workgroups of `threads`, n = first for the
+// tile's grid lines before `last0`, last from there on.  The fold's sums run
+// in an order that depends on it, so it belongs to the set's tuning (its
+// nominal tiles), whatever tiles a pass is launched over.
+struct FoldLanes {
+  int threads, first, last, last0;
+};
+
 struct TileDev {
   int plan;   // index into the plan array of the direction
   int line0;  // first line of the tile
   int nl;     // lines in the tile
   int ld;     // LDS stride in float2 (odd, >= nl)
+  FoldLanes fold;
 };
 
 // Per-thread view of a tile in LDS.  Layout of the dynamic LDS block:
@@ -510,15 +520,14 @@ __device__ __forceinline__ void fold_tail(const LineCtx& X, const PlanDev& P, co
 // (~1e-7 of the line's largest cotangent).  S lanes (a power of two,
 // S * nl <= blockDim) share a line, each summing every S-th sample with the
 // loads of eight samples (four for d > 5) in flight together, and reduce with lane shuffles
-// inside their wave.  No barrier: reads positions < N, writes side.  DD >= d
-// bounds the unrolled accumulators.
+// inside their wave.  S is that of the set's nominal tiles (FoldLanes).  No
+// barrier: reads positions < N, writes side.  DD >= d bounds the unrolled
+// accumulators.
 template <int DD>
-__device__ __forceinline__ void fold_pre_t(const LineCtx& X, int N, const float* __restrict__ G, int d) {
+__device__ __forceinline__ void fold_lines(const LineCtx& X, int N, const float* __restrict__ G, int d, int S,
+                                           int c, bool on) {
   constexpr int U = DD <= 5 ? 8 : 4;  // samples whose loads are in flight together
-  int S = 64;
-  while (S * X.nl > (int)blockDim.x) S >>= 1;
-  const int c = threadIdx.x / S, s = threadIdx.x - c * S;
-  const bool on = c < X.nl;
+  const int s = threadIdx.x & (S - 1);
   const int cc = on ? c : 0;
   const float2* __restrict__ z = X.z;
   const int ld = X.ld, w = 2 * d;
@@ -565,13 +574,33 @@ __device__ __forceinline__ void fold_pre_t(const LineCtx& X, int N, const float*
   }
 }
 
-__device__ __forceinline__ void fold_pre(const LineCtx& X, int N, const float* __restrict__ G, int d) {
+// T: the tile of grid lines, each X.nl / T.nl complex lines of the context
+// (complex line f T.nl + l belongs to grid line l).
+template <int DD>
+__device__ __forceinline__ void fold_pre_t(const LineCtx& X, int N, const float* __restrict__ G, int d,
+                                           const TileDev& T) {
+  const int F = X.nl / T.nl;
+  for (int part = 0; part < 2; ++part) {
+    const int l0 = part ? T.fold.last0 : 0, cnt = part ? T.nl - l0 : T.fold.last0;
+    if (cnt <= 0) continue;
+    int lg = 6;  // S = 2^lg
+    while (((F * (part ? T.fold.last : T.fold.first)) << lg) > T.fold.threads) --lg;
+    const int step = (int)blockDim.x >> lg;
+    for (int m0 = 0; m0 < F * cnt; m0 += step) {
+      const int m = m0 + (int)(threadIdx.x >> lg), f = m / cnt;
+      fold_lines<DD>(X, N, G, d, 1 << lg, f * T.nl + l0 + (m - f * cnt), m < F * cnt);
+    }
+  }
+}
+
+__device__ __forceinline__ void fold_pre(const LineCtx& X, int N, const float* __restrict__ G, int d,
+                                         const TileDev& T) {
   if (d <= 2)
-    fold_pre_t<2>(X, N, G, d);
+    fold_pre_t<2>(X, N, G, d, T);
   else if (d <= 5)
-    fold_pre_t<5>(X, N, G, d);
+    fold_pre_t<5>(X, N, G, d, T);
   else
-    fold_pre_t<kMaxD>(X, N, G, d);
+    fold_pre_t<kMaxD>(X, N, G, d, T);
 }
 
 // Add the fold that fold_pre left in the side buffer to the end samples
@@ -787,11 +816,12 @@ __device__ __forceinline__ void fft_apply(const LineCtx& X, const PlanDev* __res
 // conjugate multipliers, then the fold added to the end samples.
 template <bool ADJ>
 __device__ __forceinline__ void line_derivative(const LineCtx& X, const PlanDev* __restrict__ Pg, const PlanDev& P,
-                                const float* __restrict__ gqp, const double* __restrict__ dqp, int d) {
+                                const float* __restrict__ gqp, const double* __restrict__ dqp, int d,
+                                const TileDev& T) {
   if (!ADJ) {
     difference_ext(X, P, dqp + P.dq, d);
   } else {
-    if (!P.periodic) fold_pre(X, P.N, gqp + P.gq, d);
+    if (!P.periodic) fold_pre(X, P.N, gqp + P.gq, d, T);
     difference_adj(X, P);
   }
   fft_apply<ADJ>(X, Pg, P);

@@ -100,13 +100,13 @@ struct TileSet {
   size_t lds = 0;
   TileDev* d_tiles = nullptr;
   TileDev* d_tiles_bp = nullptr;
-  double estimate = 0.0;                  // of a forward pass over it (pick_forward_tiles); 0: tuned
+  double estimate = 0.0;                  // of a forward pass over it (pick_tiles); 0: tuned
 };
 
 struct DirPlan {
   std::vector<PlanDev> plans;             // one per patch
   TileSet ts[3];                          // one / two / four complex lines per grid line
-  TileSet fs[2];                          // the forward passes' tiles: one / two complex lines per grid line
+  TileSet ps[3];                          // the passes' tiles (ts when tuned, else picked for the set), like ts
   TileSet ms;                             // lines whose derivative runs as a matrix product (linemat.h)
   bool mat_large = false;                 // by the kernels for large lines
   bool any_fft = false;                   // lines that run as transforms
@@ -270,6 +270,12 @@ fcsd_status launch_tileset(const fcsd_set* s, const TileSet& D, K kern, PassArgs
   return launch_check(s->ctx, "line kernel");
 }
 
+// the same over the passes' tiles of `fields` complex lines per grid line
+template <class K>
+fcsd_status launch_pass(const fcsd_set* s, int dir, K kern, PassArgs a, int fields = 1) {
+  return launch_tileset(s, s->dir[dir - 1].ps[fields - 1], kern, a);
+}
+
 // the same over the tiles of `fields` complex lines per grid line
 template <class K>
 fcsd_status launch_lines(const fcsd_set* s, int dir, K kern, PassArgs a, int patch = -1, int fields = 1) {
@@ -310,7 +316,7 @@ fcsd_status launch_forward(const fcsd_set* s, int dir, const ForwardKernels& K, 
   }
   if (patch < 0 ? !D.any_fft : D.plans[patch].mat != 0) return FCSD_OK;
   a.fft_only = 1;
-  return launch_tileset(s, D.fs[fields - 1], K.fft, a, patch);
+  return launch_tileset(s, D.ps[fields - 1], K.fft, a, patch);
 }
 
 fcsd_status check_set(fcsd_ctx* ctx, const fcsd_set* s, int64_t plane) {
@@ -567,6 +573,7 @@ void order_tiles(const std::vector<PlanDev>& plans, TileSet& D, int order, const
   empty.line0 = 0;
   empty.nl = 0;
   empty.ld = 1;
+  empty.fold = FoldLanes{kBlock, 1, 1, 0};
   D.tiles.assign(mx * kXcd, empty);
   for (int x = 0; x < kXcd; ++x)
     for (size_t k = 0; k < lst[x].size(); ++k) D.tiles[k * kXcd + x] = lst[x][k];
@@ -604,6 +611,7 @@ void build_tileset(const std::vector<PlanDev>& plans, TileSet& D, size_t budget,
       // of one are worth far more than the conflicts (the q2 tiles of two
       // complex lines per grid line on the longest lines: 83 KB odd, 79 KB even)
       T.ld = (fields * T.nl) | 1;
+      T.fold = FoldLanes{D.threads, T.nl, T.nl, T.nl};
       if (per_ld * T.ld + tables > budget && per_ld * (fields * T.nl) + tables <= budget) T.ld = fields * T.nl;
       D.tiles_by_patch.push_back(T);
       plds = std::max(plds, per_ld * T.ld + tables);
@@ -650,17 +658,19 @@ double pass_estimate(const std::vector<PlanDev>& plans, const TileSet& D, int fi
   return end;
 }
 
-// Tile split of the forward transform passes of an untuned set: the LDS budget
-// whose estimate is least, workgroups of 512 threads (two per compute unit),
-// or the whole LDS with 1024.  A budget of 64 KB and 256 threads leaves a small
-// set with fewer workgroups than compute units, and a larger one with a last,
-// nearly empty round of them: steps of annuli of 16 x 64 x 64, 16 x 128 x 128,
-// 128 x 101 x 101 and 64 x 256 x 256 points take 817, 1004, 1227 and 3516 us
-// with it, 447, 563, 860 and 2434 at their best of 36 splits.  Results do not
-// depend on the split.  (The reverse passes, whose folds sum in an order that
-// depends on it, keep theirs.)
-void pick_forward_tiles(DirPlan& D, int f, int order, int align, int d, size_t maxlds) {
-  TileSet& F = D.fs[f];
+// Tile split of the transform passes of an untuned set on tiles of 1 << f
+// complex lines per grid line: the LDS budget whose estimate is least,
+// workgroups of 512 threads (two per compute unit), or the whole LDS with
+// 1024.  A budget of 64 KB and 256 threads leaves a small set with fewer
+// workgroups than compute units, and a larger one with a last, nearly empty
+// round of them: steps of annuli of 16 x 64 x 64, 16 x 128 x 128, 128 x 101 x
+// 101 and 64 x 256 x 256 points take 817, 1004, 1227 and 3516 us with it, 447,
+// 563, 860 and 2434 at their best of 36 splits; the reverse of a step of 16 x
+// 256 x 256 points 2.0 against 1.5 ms.  Results do not depend on the split: a
+// reverse pass folds with the lanes of the nominal tiles (ts).
+void pick_tiles(DirPlan& D, int f, int order, int align, int d, size_t maxlds) {
+  TileSet& F = D.ps[f];
+  const TileSet& nominal = D.ts[f];
   double best = 0.0;
   size_t budget = 0;
   for (size_t kb : {8, 10, 12, 14, 16, 20, 24, 28, 32, 40, 48, 56, 64, 72, 80, 160}) {
@@ -679,6 +689,14 @@ void pick_forward_tiles(DirPlan& D, int f, int order, int align, int d, size_t m
   if (!budget) F.threads = 1024;
   build_tileset(D.plans, F, F.budget, order, 1 << f, align, d);
   F.estimate = best;
+  auto lanes = [&](TileDev& T) {
+    if (T.nl == 0) return;
+    const int b = nominal.patch_begin[T.plan], e = nominal.patch_begin[T.plan + 1];
+    const TileDev &first = nominal.tiles_by_patch[b], &last = nominal.tiles_by_patch[e - 1];
+    T.fold = FoldLanes{nominal.threads, first.nl, last.nl, std::min(std::max(last.line0 - T.line0, 0), T.nl)};
+  };
+  for (TileDev& T : F.tiles) lanes(T);
+  for (TileDev& T : F.tiles_by_patch) lanes(T);
 }
 
 // Lines whose derivative runs as a matrix product (linemat.h), a rule on the
@@ -758,6 +776,7 @@ void build_mat_tiles(DirPlan& D, int order, int align, int d) {
         T.line0 = l0;
         T.nl = std::min(ncp / 4, P.nlines - l0);
         T.ld = T.nl <= 4 ? 16 : 32;
+        T.fold = FoldLanes{};
         plds = std::max(plds, mat_lds_bytes(P.mks, T.ld, P.C, d));
         cost += (long long)(P.Lx + 64) * T.ld;
         M.tiles_by_patch.push_back(T);
@@ -772,19 +791,20 @@ void build_mat_tiles(DirPlan& D, int order, int align, int d) {
 }
 
 // align: lines per tile a multiple of it (blocked storage: 4 q1 lines, 8 q2
-// lines); maxlds > 0: the forward passes' split is picked for the set
-// (untuned), else it is that of ts.
-void build_tiles(DirPlan& D, int order, int align, int d, size_t maxlds = 0) {
+// lines); maxlds > 0: the passes' splits are picked for the set (untuned),
+// else they are that of ts.
+void build_tiles(DirPlan& D, bool q2, int order, int align, int d, size_t maxlds = 0) {
   for (int f = 0; f < 3; ++f) build_tileset(D.plans, D.ts[f], D.ts[f].budget, order, 1 << f, align, d);
-  for (int f = 0; f < 2; ++f) {
-    if (maxlds) {
-      pick_forward_tiles(D, f, order, align, d, maxlds);
-    } else {
-      D.fs[f].budget = D.ts[f].budget;
-      D.fs[f].threads = D.ts[f].threads;
-      D.fs[f].estimate = 0.0;
-      build_tileset(D.plans, D.fs[f], D.fs[f].budget, order, 1 << f, align, d);
+  for (int f = 0; f < 3; ++f) {
+    // (no pass runs q1 tiles of four complex lines per grid line)
+    if (maxlds && f < (q2 ? 3 : 2)) {
+      pick_tiles(D, f, order, align, d, maxlds);
+      continue;
     }
+    D.ps[f].budget = D.ts[f].budget;
+    D.ps[f].threads = D.ts[f].threads;
+    D.ps[f].estimate = 0.0;
+    build_tileset(D.plans, D.ps[f], D.ps[f].budget, order, 1 << f, align, d);
   }
   build_mat_tiles(D, order, align, d);
 }
@@ -792,7 +812,7 @@ void build_tiles(DirPlan& D, int order, int align, int d, size_t maxlds = 0) {
 int tile_align(int layout, int dir) { return layout == FCSD_LAYOUT_B8X4 ? (dir == 0 ? 4 : 8) : 1; }
 
 fcsd_status upload_tiles(fcsd_ctx* ctx, DirPlan& D) {
-  for (TileSet* t : {&D.ts[0], &D.ts[1], &D.ts[2], &D.fs[0], &D.fs[1], &D.ms}) {
+  for (TileSet* t : {&D.ts[0], &D.ts[1], &D.ts[2], &D.ps[0], &D.ps[1], &D.ps[2], &D.ms}) {
     (void)hipFree(t->d_tiles);
     (void)hipFree(t->d_tiles_bp);
     t->d_tiles = t->d_tiles_bp = nullptr;
@@ -827,7 +847,7 @@ unsigned* set_error_word(const fcsd_set* s) { return s->d_ctr + 1 + 2 * (size_t)
 // LDS (a launch takes its largest tile's LDS; long lines, whose two-line tiles
 // need more, would halve the workgroups per CU for the whole pass).
 bool pick_a_wide(const fcsd_set* s) {
-  const TileSet &one = s->dir[0].fs[0], &two = s->dir[0].fs[1];
+  const TileSet &one = s->dir[0].ps[0], &two = s->dir[0].ps[1];
   if (one.estimate > 0.0 && two.estimate > 0.0) return two.estimate <= 2.0 * one.estimate;
   return two.lds <= std::max(one.lds, one.budget);
 }
@@ -1038,7 +1058,7 @@ extern "C" fcsd_status fcsd_set_create(fcsd_ctx* ctx, int npatch, const fcsd_pat
     for (auto& t : s->dir[dir].ts) t.budget = default_lds_budget();
     s->dir[dir].ms.budget = getenv("FCSD_LDS_BUDGET") ? default_lds_budget() : kMatBudget;
     // (a budget asked for by the environment counts as tuning)
-    build_tiles(s->dir[dir], s->tile_order, tile_align(layout, dir), d,
+    build_tiles(s->dir[dir], dir == 1, s->tile_order, tile_align(layout, dir), d,
                 getenv("FCSD_LDS_BUDGET") ? 0 : (size_t)maxlds);
   }
   {
@@ -1158,8 +1178,8 @@ extern "C" fcsd_status fcsd_set_destroy(fcsd_set* s) {
     if (g.exec) hipGraphExecDestroy(g.exec);
   for (int dir = 0; dir < 2; ++dir) {
     (void)hipFree(s->dir[dir].d_plans);
-    for (TileSet* t : {&s->dir[dir].ts[0], &s->dir[dir].ts[1], &s->dir[dir].ts[2], &s->dir[dir].fs[0],
-                       &s->dir[dir].fs[1], &s->dir[dir].ms}) {
+    for (TileSet* t : {&s->dir[dir].ts[0], &s->dir[dir].ts[1], &s->dir[dir].ts[2], &s->dir[dir].ps[0],
+                       &s->dir[dir].ps[1], &s->dir[dir].ps[2], &s->dir[dir].ms}) {
       (void)hipFree(t->d_tiles);
       (void)hipFree(t->d_tiles_bp);
     }
@@ -1234,7 +1254,7 @@ extern "C" fcsd_status fcsd_set_tune(fcsd_set* s, const int lds_budget[3], const
   fcsd_status r;
   for (int dir = 0; dir < 2; ++dir) {
     DirPlan& D = s->dir[dir];
-    build_tiles(D, order, tile_align(s->layout, dir), s->d);
+    build_tiles(D, dir == 1, order, tile_align(s->layout, dir), s->d);
     if (dir == 1) {
       // q2 tiles of four complex lines per grid line (the wide fused pass,
       // the reverse mode's q2 pass): when their tiles exceed the third
@@ -1245,6 +1265,10 @@ extern "C" fcsd_status fcsd_set_tune(fcsd_set* s, const int lds_budget[3], const
         W.budget = (size_t)maxlds;
         W.threads = 1024;
         build_tileset(D.plans, W, W.budget, order, 4, tile_align(s->layout, dir), s->d);
+        TileSet& R = D.ps[2];
+        R.budget = W.budget;
+        R.threads = W.threads;
+        build_tileset(D.plans, R, R.budget, order, 4, tile_align(s->layout, dir), s->d);
       }
     }
     if ((r = upload_tiles(ctx, D))) return r;
@@ -1388,7 +1412,7 @@ extern "C" fcsd_status fc_diff_adj(fcsd_ctx* ctx, const fcsd_set* s, int dir, in
   a.nf = nf;
   a.in = out_bar;
   a.out = in_bar;
-  return dir == 1 ? launch_lines(s, 1, k_fcdiff<1, true>, a) : launch_lines(s, 2, k_fcdiff<2, true>, a);
+  return launch_pass(s, dir, dir == 1 ? k_fcdiff<1, true> : k_fcdiff<2, true>, a);
 }
 
 extern "C" fcsd_status fc_continue(fcsd_ctx* ctx, const fcsd_set* s, int dir, int nf, const float* in,
@@ -1983,12 +2007,12 @@ fcsd_status filter_impl(fcsd_ctx* ctx, const fcsd_set* s, const float* in, float
   a.gamma = gamma;
   a.in = in;
   a.out = out;
-  fcsd_status st = launch_tileset(s, s->dir[0].fs[1], k_filter<1>, a);
+  fcsd_status st = launch_pass(s, 1, k_filter<1>, a, 2);
   if (st) return st;
   PassArgs b = a;
   b.plans = s->dir[1].d_plans;
   b.in = out;
-  return launch_tileset(s, s->dir[1].fs[1], k_filter<2>, b);
+  return launch_pass(s, 2, k_filter<2>, b, 2);
 }
 
 // Reverse mode of filter_impl at state e: out_bar (cotangent of the
@@ -2004,13 +2028,13 @@ fcsd_status filter_adj_impl(fcsd_ctx* ctx, const fcsd_set* s, const float* e, co
   a.in = out_bar;
   a.u = w;
   a.out = w + 4 * pl;
-  if ((st = launch_lines(s, 2, k_filter_adj<2>, a, -1, 2))) return st;
+  if ((st = launch_pass(s, 2, k_filter_adj<2>, a, 2))) return st;
   PassArgs b = base_args(s, 1);
   b.gamma = gamma;
   b.in = w + 4 * pl;
   b.u = e;
   b.out = u_bar;
-  return launch_lines(s, 1, k_filter_adj<1>, b, -1, 2);
+  return launch_pass(s, 1, k_filter_adj<1>, b, 2);
 }
 
 // planes of a step record after the stage inputs, mu, the maximisers and the
@@ -2693,8 +2717,8 @@ fcsd_status rhs_adj_impl(fcsd_ctx* ctx, const fcsd_set* s, const float* u, const
     const DirPlan& D = s->dir[0];
     PassArgs b = a;
     b.plans = D.d_plans;
-    b.tiles = D.ts[0].d_tiles;
-    hipLaunchKernelGGL(k_adjHb1, dim3((unsigned)D.ts[0].tiles.size()), dim3(D.ts[0].threads), D.ts[0].lds,
+    b.tiles = D.ps[0].d_tiles;
+    hipLaunchKernelGGL(k_adjHb1, dim3((unsigned)D.ps[0].tiles.size()), dim3(D.ps[0].threads), D.ps[0].lds,
                        ctx->stream, b, rhs_bar, Hb);
     if ((st = launch_check(ctx, "adj C"))) return st;
   }
@@ -2706,17 +2730,17 @@ fcsd_status rhs_adj_impl(fcsd_ctx* ctx, const fcsd_set* s, const float* u, const
     const DirPlan& D = s->dir[1];
     PassArgs b = a;
     b.plans = D.d_plans;
-    b.tiles = D.ts[1].d_tiles;
+    b.tiles = D.ps[1].d_tiles;
     if (wide) {
-      b.tiles = D.ts[2].d_tiles;
-      hipLaunchKernelGGL(k_adjHb2w, dim3((unsigned)D.ts[2].tiles.size()), dim3(D.ts[2].threads), D.ts[2].lds,
+      b.tiles = D.ps[2].d_tiles;
+      hipLaunchKernelGGL(k_adjHb2w, dim3((unsigned)D.ps[2].tiles.size()), dim3(D.ps[2].threads), D.ps[2].lds,
                          ctx->stream, b, rhs_bar, (const float*)Hb, (const float*)d1e, (const float*)d2e, G1, mu_bar,
                          u_bar);
     } else if (visc)
-      hipLaunchKernelGGL(k_adjHb2p<true>, dim3((unsigned)D.ts[1].tiles.size()), dim3(D.ts[1].threads), D.ts[1].lds,
+      hipLaunchKernelGGL(k_adjHb2p<true>, dim3((unsigned)D.ps[1].tiles.size()), dim3(D.ps[1].threads), D.ps[1].lds,
                          ctx->stream, b, rhs_bar, Hb, (const float*)d1e, (const float*)d2e, G1, G2, mu_bar, u_bar);
     else
-      hipLaunchKernelGGL(k_adjHb2p<false>, dim3((unsigned)D.ts[1].tiles.size()), dim3(D.ts[1].threads), D.ts[1].lds,
+      hipLaunchKernelGGL(k_adjHb2p<false>, dim3((unsigned)D.ps[1].tiles.size()), dim3(D.ps[1].threads), D.ps[1].lds,
                          ctx->stream, b, rhs_bar, Hb, (const float*)d1e, (const float*)d2e, G1, G2, mu_bar, u_bar);
     if ((st = launch_check(ctx, "adj B2"))) return st;
   }

@@ -182,7 +182,7 @@ __global__ void FCSD_LINE_BOUNDS k_fcdiff(PassArgs a) {
           M.w, [&](unsigned g) { return make_float2(at(A, g), at(B, g)); },
           [&](unsigned, unsigned l, float2 v) { at(z, l) = make_float2(v.x, two ? v.y : 0.f); });
       __syncthreads();
-      line_derivative<true>(X, Pg, P, a.gq, a.dq, a.d);
+      line_derivative<true>(X, Pg, P, a.gq, a.dq, a.d, T);
     }
     float* OA = a.out + (long long)f * a.plane + M.base;
     float* OB = two ? a.out + (long long)(f + 1) * a.plane + M.base : OA;
@@ -681,7 +681,7 @@ __global__ void FCSD_LINE_BOUNDS k_filter_adj(PassArgs a) {
   zero_tail(X, P);
   __syncthreads();
   if (!P.periodic) {
-    fold_pre(X, P.N, a.gf + P.gf, a.d);
+    fold_pre(X, P.N, a.gf + P.gf, a.d, T);
     __syncthreads();
   }
   fft_apply<true>(X, Pg, P);

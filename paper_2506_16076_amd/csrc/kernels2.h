@@ -1687,7 +1687,7 @@ __global__ void FCSD_LINE_BOUNDS k_adjHb1(PassArgs a, const float* rb, float* Hb
         M.w, [&](unsigned g) { return make_float4(at(rbc, g), at(mdx, g), at(mdy, g), 0.f); },
         [&](unsigned, unsigned l, float4 v) { at(z, l) = make_float2(v.y * v.x, v.z * v.x); });
     __syncthreads();
-    line_derivative<true>(X, Pg, P, a.gq, a.dq, a.d);
+    line_derivative<true>(X, Pg, P, a.gq, a.dq, a.d, T);
     float* hbx = Hb + (2 * comp) * pl + bo;
     float* hby = Hb + (2 * comp + 1) * pl + bo;
     walk(M.w, [&](unsigned g, unsigned l) {
@@ -1739,7 +1739,7 @@ __global__ void FCSD_LINE_BOUNDS k_adjHb2p(PassArgs a, const float* rb, float* H
           at(zb, l) = make_float2(q.mx * q.r1, q.my * q.r1);
         });
     __syncthreads();
-    line_derivative<true>(X, Pg, P, a.gq, a.dq, a.d);
+    line_derivative<true>(X, Pg, P, a.gq, a.dq, a.d, T);
     float* hb0 = Hb + (2 * comp) * pl + bo;   // x, y of comp; then of comp + 1
     const long long fo = comp * pl + bo;
     if (!VISC) {
@@ -1834,8 +1834,8 @@ __global__ void FCSD_LINE_BOUNDS k_adjHb2p(PassArgs a, const float* rb, float* H
 // lines per grid line), mu_bar and, unless mode is FLUX_VISC, the flux VJP
 // of -Hb into u_bar, so that Hb itself is never stored; then u_bar +=
 // D_2^T G2.  The same FP32 operations as k_adjHb2p followed by fc_diff_adj
-// of G2 along q2, up to the order of the tail folds' sums (fold_pre splits
-// a line over a number of lanes that depends on the tile's line count).
+// of G2 along q2, up to the order of the tail folds' sums (FoldLanes differ
+// between the tile sets).
 __global__ void FCSD_LINE_BOUNDS k_adjHb2w(PassArgs a, const float* rb, const float* Hb, const float* d1e,
                                           const float* d2e, float* G1, float* mub, float* ub) {
   const TileDev T = a.tiles[blockIdx.x];
@@ -1878,7 +1878,7 @@ __global__ void FCSD_LINE_BOUNDS k_adjHb2w(PassArgs a, const float* rb, const fl
         at(z3, l) = make_float2(q.mx * q.r[3], q.my * q.r[3]);
       });
   __syncthreads();
-  line_derivative<true>(X4, Pg, P, a.gq, a.dq, a.d);
+  line_derivative<true>(X4, Pg, P, a.gq, a.dq, a.d, T);
   const bool flux = a.mode != FLUX_VISC;
   float* mubp = mub ? mub + bo : nullptr;
   struct VIn4 {
@@ -1936,7 +1936,7 @@ __global__ void FCSD_LINE_BOUNDS k_adjHb2w(PassArgs a, const float* rb, const fl
       });
   __syncthreads();
   // u_bar += D_2^T G2 (G2 of components 0, 1 and 2, 3 as two complex lines)
-  line_derivative<true>(X2, Pg, P, a.gq, a.dq, a.d);
+  line_derivative<true>(X2, Pg, P, a.gq, a.dq, a.d, T);
   walk_b<kLoadBatch>(
       M.w,
       [&](unsigned g) {

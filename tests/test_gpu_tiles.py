@@ -1,6 +1,7 @@
-"""The forward passes' tile split that an untuned set picks for itself changes no
-bit: derivatives, right-hand side and filter of untuned sets equal those of the
-same sets tuned to other splits."""
+"""The passes' tile split that an untuned set picks for itself changes no bit:
+derivatives, right-hand side and filter of untuned sets equal those of the same
+sets tuned to other splits, their reverse modes (whose folds belong to the
+nominal split) those of the sets tuned to the nominal one."""
 import numpy as np
 import pytest
 
@@ -56,3 +57,35 @@ def test_untuned_split_changes_no_bit(env, name, layout):
     for o in outs[1:]:
         for a, b in zip(o, outs[0]):
             assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("name", [k for k in CASES if k != "long lines"])
+def test_untuned_split_changes_no_bit_of_the_reverse(env, name, layout):
+    api, ctx, torch = env
+    cfg = CASES[name]()
+    ps = cfg.ps
+    rng = np.random.default_rng(4)
+    bar = rng.standard_normal((4, ps.plane)).astype(np.float32)
+    outs = []
+    for tune in (None, (65536, 256)):
+        s = api.PatchSet.from_layout(ctx, ps, layout)
+        if tune:
+            s.tune(*tune)
+        s.set_filter(10.0, 14)
+        u, metric = s.to_device(cfg.u0), s.to_device(ps.metric)
+        mu = s.to_device(np.full((1, ps.plane), 1e-3, np.float32))
+        rb = s.to_device(bar)
+        ub, e1, e2, d1, d2, fb = (torch.zeros_like(u) for _ in range(6))
+        mb = torch.zeros_like(mu)
+        api.fcsd_rhs_adj(s, u, metric, mu, cfg.ref, 1.4, rb, ub, mb)
+        api.euler_rhs_adj(s, u, metric, cfg.ref, 1.4, rb, e1)
+        s.set_schedule(0)
+        api.fcsd_rhs_adj(s, u, metric, mu, cfg.ref, 1.4, rb, e2)
+        api.fc_diff_adj(s, 1, rb, d1, 4)
+        api.fc_diff_adj(s, 2, rb, d2, 4)
+        api.fcsd_filter_adj(s, u, rb, fb, 1.4)
+        outs.append([s.to_host(t) for t in (ub, e1, e2, d1, d2, fb)] + [s.to_host(mb)])
+        s.close()
+    for a, b in zip(*outs):
+        assert np.array_equal(a, b)
