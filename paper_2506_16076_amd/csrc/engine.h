@@ -76,7 +76,8 @@ struct TileDev {
   int line0;  // first line of the tile
   int nl;     // lines in the tile
   int ld;     // LDS stride in float2 (odd, >= nl)
-  FoldLanes fold;
+  FoldLanes fold;   // nominal tiles of the same kind
+  FoldLanes fold1;  // those of one complex line per grid line
 };
 
 // Per-thread view of a tile in LDS.  Layout of the dynamic LDS block:
@@ -575,16 +576,19 @@ __device__ __forceinline__ void fold_lines(const LineCtx& X, int N, const float*
 }
 
 // T: the tile of grid lines, each X.nl / T.nl complex lines of the context
-// (complex line f T.nl + l belongs to grid line l).
+// (complex line f T.nl + l belongs to grid line l); W: nominal tiles of W
+// complex lines per grid line (1: fold1), 0: of as many as the context's.
 template <int DD>
 __device__ __forceinline__ void fold_pre_t(const LineCtx& X, int N, const float* __restrict__ G, int d,
-                                           const TileDev& T) {
+                                           const TileDev& T, int W) {
   const int F = X.nl / T.nl;
+  const FoldLanes Q = W == 1 ? T.fold1 : T.fold;
+  if (W == 0) W = F;
   for (int part = 0; part < 2; ++part) {
-    const int l0 = part ? T.fold.last0 : 0, cnt = part ? T.nl - l0 : T.fold.last0;
+    const int l0 = part ? Q.last0 : 0, cnt = part ? T.nl - l0 : Q.last0;
     if (cnt <= 0) continue;
     int lg = 6;  // S = 2^lg
-    while (((F * (part ? T.fold.last : T.fold.first)) << lg) > T.fold.threads) --lg;
+    while (((W * (part ? Q.last : Q.first)) << lg) > Q.threads) --lg;
     const int step = (int)blockDim.x >> lg;
     for (int m0 = 0; m0 < F * cnt; m0 += step) {
       const int m = m0 + (int)(threadIdx.x >> lg), f = m / cnt;
@@ -594,13 +598,13 @@ __device__ __forceinline__ void fold_pre_t(const LineCtx& X, int N, const float*
 }
 
 __device__ __forceinline__ void fold_pre(const LineCtx& X, int N, const float* __restrict__ G, int d,
-                                         const TileDev& T) {
+                                         const TileDev& T, int W = 0) {
   if (d <= 2)
-    fold_pre_t<2>(X, N, G, d, T);
+    fold_pre_t<2>(X, N, G, d, T, W);
   else if (d <= 5)
-    fold_pre_t<5>(X, N, G, d, T);
+    fold_pre_t<5>(X, N, G, d, T, W);
   else
-    fold_pre_t<kMaxD>(X, N, G, d, T);
+    fold_pre_t<kMaxD>(X, N, G, d, T, W);
 }
 
 // Add the fold that fold_pre left in the side buffer to the end samples
@@ -817,11 +821,11 @@ __device__ __forceinline__ void fft_apply(const LineCtx& X, const PlanDev* __res
 template <bool ADJ>
 __device__ __forceinline__ void line_derivative(const LineCtx& X, const PlanDev* __restrict__ Pg, const PlanDev& P,
                                 const float* __restrict__ gqp, const double* __restrict__ dqp, int d,
-                                const TileDev& T) {
+                                const TileDev& T, int W = 0) {
   if (!ADJ) {
     difference_ext(X, P, dqp + P.dq, d);
   } else {
-    if (!P.periodic) fold_pre(X, P.N, gqp + P.gq, d, T);
+    if (!P.periodic) fold_pre(X, P.N, gqp + P.gq, d, T, W);
     difference_adj(X, P);
   }
   fft_apply<ADJ>(X, Pg, P);

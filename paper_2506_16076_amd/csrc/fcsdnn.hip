@@ -107,6 +107,7 @@ struct DirPlan {
   std::vector<PlanDev> plans;             // one per patch
   TileSet ts[3];                          // one / two / four complex lines per grid line
   TileSet ps[3];                          // the passes' tiles (ts when tuned, else picked for the set), like ts
+  bool two_rounds = false;                // passes over four components: two rounds on ps[1], not four on ps[0]
   TileSet ms;                             // lines whose derivative runs as a matrix product (linemat.h)
   bool mat_large = false;                 // by the kernels for large lines
   bool any_fft = false;                   // lines that run as transforms
@@ -573,7 +574,7 @@ void order_tiles(const std::vector<PlanDev>& plans, TileSet& D, int order, const
   empty.line0 = 0;
   empty.nl = 0;
   empty.ld = 1;
-  empty.fold = FoldLanes{kBlock, 1, 1, 0};
+  empty.fold = empty.fold1 = FoldLanes{kBlock, 1, 1, 0};
   D.tiles.assign(mx * kXcd, empty);
   for (int x = 0; x < kXcd; ++x)
     for (size_t k = 0; k < lst[x].size(); ++k) D.tiles[k * kXcd + x] = lst[x][k];
@@ -611,7 +612,7 @@ void build_tileset(const std::vector<PlanDev>& plans, TileSet& D, size_t budget,
       // of one are worth far more than the conflicts (the q2 tiles of two
       // complex lines per grid line on the longest lines: 83 KB odd, 79 KB even)
       T.ld = (fields * T.nl) | 1;
-      T.fold = FoldLanes{D.threads, T.nl, T.nl, T.nl};
+      T.fold = T.fold1 = FoldLanes{D.threads, T.nl, T.nl, T.nl};
       if (per_ld * T.ld + tables > budget && per_ld * (fields * T.nl) + tables <= budget) T.ld = fields * T.nl;
       D.tiles_by_patch.push_back(T);
       plds = std::max(plds, per_ld * T.ld + tables);
@@ -689,11 +690,15 @@ void pick_tiles(DirPlan& D, int f, int order, int align, int d, size_t maxlds) {
   if (!budget) F.threads = 1024;
   build_tileset(D.plans, F, F.budget, order, 1 << f, align, d);
   F.estimate = best;
+  auto lanes_of = [](const TileSet& n, const TileDev& T) {
+    const TileDev &first = n.tiles_by_patch[n.patch_begin[T.plan]];
+    const TileDev &last = n.tiles_by_patch[n.patch_begin[T.plan + 1] - 1];
+    return FoldLanes{n.threads, first.nl, last.nl, std::min(std::max(last.line0 - T.line0, 0), T.nl)};
+  };
   auto lanes = [&](TileDev& T) {
     if (T.nl == 0) return;
-    const int b = nominal.patch_begin[T.plan], e = nominal.patch_begin[T.plan + 1];
-    const TileDev &first = nominal.tiles_by_patch[b], &last = nominal.tiles_by_patch[e - 1];
-    T.fold = FoldLanes{nominal.threads, first.nl, last.nl, std::min(std::max(last.line0 - T.line0, 0), T.nl)};
+    T.fold = lanes_of(nominal, T);
+    T.fold1 = lanes_of(D.ts[0], T);
   };
   for (TileDev& T : F.tiles) lanes(T);
   for (TileDev& T : F.tiles_by_patch) lanes(T);
@@ -776,7 +781,7 @@ void build_mat_tiles(DirPlan& D, int order, int align, int d) {
         T.line0 = l0;
         T.nl = std::min(ncp / 4, P.nlines - l0);
         T.ld = T.nl <= 4 ? 16 : 32;
-        T.fold = FoldLanes{};
+        T.fold = T.fold1 = FoldLanes{};
         plds = std::max(plds, mat_lds_bytes(P.mks, T.ld, P.C, d));
         cost += (long long)(P.Lx + 64) * T.ld;
         M.tiles_by_patch.push_back(T);
@@ -850,6 +855,16 @@ bool pick_a_wide(const fcsd_set* s) {
   const TileSet &one = s->dir[0].ps[0], &two = s->dir[0].ps[1];
   if (one.estimate > 0.0 && two.estimate > 0.0) return two.estimate <= 2.0 * one.estimate;
   return two.lds <= std::max(one.lds, one.budget);
+}
+
+// Passes over four components (pass C; the reverse mode's transposed
+// derivatives) run two a round on the tiles of two complex lines per grid line
+// when two such rounds are estimated faster than four on the one-line tiles
+// (untuned sets), by more than a tenth (the estimate leaves out that their
+// epilogues hold two points' registers).
+bool pick_two_rounds(const DirPlan& D) {
+  const TileSet &one = D.ps[0], &two = D.ps[1];
+  return one.estimate > 0.0 && two.estimate > 0.0 && 2.0 * two.estimate < 0.9 * 4.0 * one.estimate;
 }
 
 // Task queue of the persistent stage kernel from the current tile sets:
@@ -1072,6 +1087,7 @@ extern "C" fcsd_status fcsd_set_create(fcsd_ctx* ctx, int npatch, const fcsd_pat
     // the wide fused q2 pass (four complex lines per grid line) is optional
     s->wide_ok = s->dir[1].ts[2].lds <= (size_t)maxlds;
     s->a_wide = pick_a_wide(s.get());
+    for (auto& D : s->dir) D.two_rounds = pick_two_rounds(D);
   }
   // per-patch descriptors and point chunks
   std::vector<PatchDev> pd;
@@ -1276,6 +1292,7 @@ extern "C" fcsd_status fcsd_set_tune(fcsd_set* s, const int lds_budget[3], const
   if ((r = build_stage_tasks(s))) return r;
   s->wide_ok = s->dir[1].ts[2].lds <= (size_t)maxlds;
   s->a_wide = pick_a_wide(s);
+  for (auto& D : s->dir) D.two_rounds = pick_two_rounds(D);
   if ((s->schedule == FCSD_SCHED_PERSISTENT && !s->persistent_ok) ||
       (s->schedule == FCSD_SCHED_FUSED_WIDE && !s->wide_ok))
     s->schedule = FCSD_SCHED_FUSED;
@@ -1412,6 +1429,8 @@ extern "C" fcsd_status fc_diff_adj(fcsd_ctx* ctx, const fcsd_set* s, int dir, in
   a.nf = nf;
   a.in = out_bar;
   a.out = in_bar;
+  if (nf % 4 == 0 && s->dir[dir - 1].two_rounds)
+    return launch_pass(s, dir, dir == 1 ? k_fcdiff_adj2<1> : k_fcdiff_adj2<2>, a, 2);
   return launch_pass(s, dir, dir == 1 ? k_fcdiff<1, true> : k_fcdiff<2, true>, a);
 }
 
@@ -1621,7 +1640,9 @@ fcsd_status rhs_passes(fcsd_ctx* ctx, const fcsd_set* s, const float* u, const f
     if ((st = launch_forward(s, 2, ForwardKernels{{k_mat_B2<MatSmall>, k_mat_B2<MatLarge>}, k_passB2}, a, patch))) return st;
   }
   if (!(passes & 8u)) return FCSD_OK;
-  return launch_forward(s, 1, ForwardKernels{{k_mat_C<MatSmall>, k_mat_C<MatLarge>}, k_passC}, e, patch);
+  const bool two = s->dir[0].two_rounds;
+  return launch_forward(s, 1, ForwardKernels{{k_mat_C<MatSmall>, k_mat_C<MatLarge>}, two ? k_passC2 : k_passC}, e,
+                        patch, two ? 2 : 1);
 }
 
 }  // namespace
@@ -2717,9 +2738,10 @@ fcsd_status rhs_adj_impl(fcsd_ctx* ctx, const fcsd_set* s, const float* u, const
     const DirPlan& D = s->dir[0];
     PassArgs b = a;
     b.plans = D.d_plans;
-    b.tiles = D.ps[0].d_tiles;
-    hipLaunchKernelGGL(k_adjHb1, dim3((unsigned)D.ps[0].tiles.size()), dim3(D.ps[0].threads), D.ps[0].lds,
-                       ctx->stream, b, rhs_bar, Hb);
+    const TileSet& Q = D.ps[D.two_rounds];
+    b.tiles = Q.d_tiles;
+    hipLaunchKernelGGL(D.two_rounds ? k_adjHb1<2> : k_adjHb1<1>, dim3((unsigned)Q.tiles.size()), dim3(Q.threads),
+                       Q.lds, ctx->stream, b, rhs_bar, Hb);
     if ((st = launch_check(ctx, "adj C"))) return st;
   }
   // the viscous q2 reverse on tiles of all four components, with the q2

@@ -205,6 +205,45 @@ __global__ void FCSD_LINE_BOUNDS k_fcdiff(PassArgs a) {
   }
 }
 
+// fc_diff_adj of four fields a round, on tiles of two complex lines per grid
+// line (folded as on those of one: the same bits as k_fcdiff<DIR, true>).
+template <int DIR>
+__global__ void FCSD_LINE_BOUNDS k_fcdiff_adj2(PassArgs a) {
+  const TileDev T = a.tiles[blockIdx.x];
+  if (T.nl == 0) return;
+  const PlanDev P = a.plans[T.plan];
+  const PlanDev* Pg = a.plans + T.plan;
+  TileDev T2 = T;
+  T2.nl = 2 * T.nl;
+  const LineCtx X = line_setup(lds_z, T2, P, a.tw, a.km);
+  float2 *z = X.z, *zb = X.z + T.nl;
+  const long long pl = a.plane;
+  const TileMem M = tile_mem<DIR>(P, T, T.nl, T.ld);
+  __syncthreads();
+  for (int f = 0; f < a.nf; f += 4) {
+    const float* A = a.in + (long long)f * pl + M.base;
+    walk_b<kEpiBatch>(
+        M.w, [&](unsigned g) { return make_float4(at(A, g), at(A + pl, g), at(A + 2 * pl, g), at(A + 3 * pl, g)); },
+        [&](unsigned, unsigned l, float4 v) {
+          at(z, l) = make_float2(v.x, v.y);
+          at(zb, l) = make_float2(v.z, v.w);
+        });
+    __syncthreads();
+    line_derivative<true>(X, Pg, P, a.gq, a.dq, a.d, T, 1);
+    float* O = a.out + (long long)f * pl + M.base;
+    walk_b<kEpiBatch>(
+        M.w, [&](unsigned g) { return make_float4(at(O, g), at(O + pl, g), at(O + 2 * pl, g), at(O + 3 * pl, g)); },
+        [&](unsigned g, unsigned l, float4 o) {
+          const float2 v = at(z, l), w = at(zb, l);
+          at(O, g) = o.x + v.x;
+          at(O + pl, g) = o.y + v.y;
+          at(O + 2 * pl, g) = o.z + w.x;
+          at(O + 3 * pl, g) = o.w + w.y;
+        });
+    __syncthreads();
+  }
+}
+
 // fc_continue (FWD) and its transpose: ext lines of length L per plan
 // (line c of the tile at ext offset e0 + c L, row-major).
 template <int DIR, bool ADJ>
@@ -824,6 +863,102 @@ __device__ __forceinline__ void passC_tile(const PassArgs& a, const TileDev& Tin
         });
     __syncthreads();
   }
+}
+
+// Pass C two components a round, on a q1 tile that holds two complex lines per
+// grid line: half as many rounds of load, transform and store, each a chain of
+// barriers that small sets wait for (steps of annuli of 16 x 64 x 64, 16 x 128
+// x 128 and 128 x 101 x 101 points 439 -> 378, 566 -> 502 and 878 -> 797 us;
+// 64 x 256 x 256 2458 -> 2504: large sets are better off with the one-line
+// tiles' more lines a tile, see pick_two_rounds).  The
+// same FP32 operations on every line and point as passC_tile.
+__device__ __forceinline__ void passC2_tile(const PassArgs& a, const TileDev& T, float2* lds) {
+  const PlanDev P = a.plans[T.plan];
+  const PlanDev* Pg = a.plans + T.plan;
+  TileDev T2 = T;
+  T2.nl = 2 * T.nl;
+  const LineCtx X = line_setup(lds, T2, P, a.tw, a.km);
+  float2* __restrict__ z = X.z;
+  const int N = P.N, nl = T.nl, ld = T.ld;
+  const TileMem M = tile_mem<1>(P, T, nl, ld);
+  const long long pl = a.plane;
+  float dt = 0.f;
+  const RkCoef K = rk_coef(a.stage);
+  if (a.mode == MODE_RK) dt = a.dt[0];
+  const float* m1x = a.metric + M.base;
+  const float* m1y = a.metric + pl + M.base;
+  float2* __restrict__ zb = z + nl;
+  (void)N;
+  __syncthreads();
+  for (int comp = 0; comp < 4; comp += 2) {
+    const float* A = a.H + (2 * comp) * pl + M.base;
+    load_plain(X, M.w, 0, A, A + pl);
+    load_plain(X, M.w, nl, A + 2 * pl, A + 3 * pl);
+    __syncthreads();
+    difference_ext(X, P, a.dq + P.dq, a.d);
+    fft_apply<false>(X, Pg, P);
+    const long long fo = comp * pl + M.base;
+    const float* r2c = a.r2 + fo;
+    const bool rk = a.mode == MODE_RK;
+    const float* uic = rk ? a.ui + fo : r2c;
+    const float* wc = a.mode == MODE_ADD ? a.rhs + fo : ((rk && a.stage >= 3) ? a.acc + fo : r2c);
+    const float* u0c = (rk && a.stage <= 3) ? a.u0 + fo : r2c;
+    float* rhs = a.rhs + fo;
+    float* uout = a.uout + fo;
+    float* acc = a.acc + fo;
+    struct CIn {
+      float m1x, m1y, r2[2], ui[2], w[2], u0[2];
+    };
+    walk_b<4>(
+        M.w,
+        [&](unsigned g) {
+          CIn q;
+          q.m1x = at(m1x, g);
+          q.m1y = at(m1y, g);
+#pragma unroll
+          for (int k = 0; k < 2; ++k) {
+            q.r2[k] = at(r2c + k * pl, g);
+            q.ui[k] = at(uic + k * pl, g);
+            q.w[k] = at(wc + k * pl, g);
+            q.u0[k] = at(u0c + k * pl, g);
+          }
+          return q;
+        },
+        [&](unsigned g, unsigned l, const CIn& q) {
+          const float2 v2[2] = {at(z, l), at(zb, l)};
+#pragma unroll
+          for (int k = 0; k < 2; ++k) {
+            const float2 v = v2[k];
+            const float r = q.m1x * v.x + q.m1y * v.y + q.r2[k];
+            if (a.mode == MODE_SET) {
+              at(rhs + k * pl, g) = r;
+            } else if (a.mode == MODE_ADD) {
+              at(rhs + k * pl, g) = q.w[k] + r;
+            } else {
+              const float ui = q.ui[k];
+              const float dr = dt * r;
+              if (a.stage <= 1) {
+                at(uout + k * pl, g) = K.a0 * q.u0[k] + K.ai * ui + K.b * dr;
+              } else if (a.stage == 2) {
+                at(uout + k * pl, g) = K.a0 * q.u0[k] + K.ai * ui + K.b * dr;
+                at(acc + k * pl, g) = K.acc_i * ui;
+              } else if (a.stage == 3) {
+                at(uout + k * pl, g) = K.a0 * q.u0[k] + K.ai * ui + K.b * dr;
+                at(acc + k * pl, g) = q.w[k] + (K.acc_i * ui + K.acc_b * dr);
+              } else {
+                at(uout + k * pl, g) = q.w[k] + K.ai * ui + K.b * dr;
+              }
+            }
+          }
+        });
+    __syncthreads();
+  }
+}
+
+__global__ void FCSD_LINE_BOUNDS k_passC2(PassArgs a) {
+  const TileDev T = a.tiles[blockIdx.x];
+  if (T.nl == 0 || (a.fft_only && a.plans[T.plan].mat)) return;
+  passC2_tile(a, T, lds_z);
 }
 
 __global__ void FCSD_LINE_BOUNDS k_passC(PassArgs a) {

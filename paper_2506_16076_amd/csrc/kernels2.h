@@ -1670,30 +1670,58 @@ __device__ __forceinline__ void flux_vjp(const float e[4], float gam, const floa
 }
 
 // Reverse of pass C: Hb = D_1^T (m_1x rb, m_1y rb) for every state
-// component (q1 lines).  The reverse of pass B2, which also finishes H_bar
-// and applies the pointwise reverse of H = mu grad e - f', is k_adjHb2p.
+// component (q1 lines), CW components a round on tiles of CW complex lines per
+// grid line (folded as on those of one: the same bits for either).  The
+// reverse of pass B2, which also finishes H_bar and applies the pointwise
+// reverse of H = mu grad e - f', is k_adjHb2p.
+template <int CW>
 __global__ void FCSD_LINE_BOUNDS k_adjHb1(PassArgs a, const float* rb, float* Hb) {
-  FCSD_TILE_BEGIN(a)
-  const TileMem M = tile_mem<1>(P, T, nl, ld);
+  const TileDev T = a.tiles[blockIdx.x];
+  if (T.nl == 0) return;
+  const PlanDev P = a.plans[T.plan];
+  const PlanDev* Pg = a.plans + T.plan;
+  TileDev TW = T;
+  TW.nl = CW * T.nl;
+  const LineCtx X = line_setup(lds_z, TW, P, a.tw, a.km);
+  float2* __restrict__ z = X.z;
+  const int nl = T.nl;
+  const TileMem M = tile_mem<1>(P, T, nl, T.ld);
   const long long pl = a.plane, bo = M.base;
   const float* mdx = a.metric + bo;
   const float* mdy = a.metric + pl + bo;
+  struct RIn {
+    float mx, my, r[CW];
+  };
+  __syncthreads();
   // loads of the element loops are batched (walk_b): one element's loads
   // waited for before the next element's were issued made this kernel
   // latency-bound
-  for (int comp = 0; comp < 4; ++comp) {
+  for (int comp = 0; comp < 4; comp += CW) {
     const float* rbc = rb + comp * pl + bo;
     walk_b<kLoadBatch>(
-        M.w, [&](unsigned g) { return make_float4(at(rbc, g), at(mdx, g), at(mdy, g), 0.f); },
-        [&](unsigned, unsigned l, float4 v) { at(z, l) = make_float2(v.y * v.x, v.z * v.x); });
+        M.w,
+        [&](unsigned g) {
+          RIn q;
+          q.mx = at(mdx, g);
+          q.my = at(mdy, g);
+#pragma unroll
+          for (int k = 0; k < CW; ++k) q.r[k] = at(rbc + k * pl, g);
+          return q;
+        },
+        [&](unsigned, unsigned l, const RIn& q) {
+#pragma unroll
+          for (int k = 0; k < CW; ++k) at(z + k * nl, l) = make_float2(q.mx * q.r[k], q.my * q.r[k]);
+        });
     __syncthreads();
-    line_derivative<true>(X, Pg, P, a.gq, a.dq, a.d, T);
-    float* hbx = Hb + (2 * comp) * pl + bo;
-    float* hby = Hb + (2 * comp + 1) * pl + bo;
+    line_derivative<true>(X, Pg, P, a.gq, a.dq, a.d, T, 1);
+    float* hb = Hb + (2 * comp) * pl + bo;
     walk(M.w, [&](unsigned g, unsigned l) {
-      const float2 v = at(z, l);
-      at(hbx, g) = v.x;
-      at(hby, g) = v.y;
+#pragma unroll
+      for (int k = 0; k < CW; ++k) {
+        const float2 v = at(z + k * nl, l);
+        at(hb + (2 * k) * pl, g) = v.x;
+        at(hb + (2 * k + 1) * pl, g) = v.y;
+      }
     });
     __syncthreads();
   }
