@@ -186,6 +186,7 @@ struct fcsd_set {
   size_t stage_lds = 0;
   int stage_threads = 0;
   bool wide_ok = false;                   // the q2 tiles of four complex lines per grid line fit the LDS
+  bool b_wide = false;                    // the fused q2 pass on tiles of four complex lines per grid line
   bool a_wide = false;                    // pass A on the q1 tiles of two complex lines per grid line
 };
 
@@ -317,7 +318,7 @@ fcsd_status launch_forward(const fcsd_set* s, int dir, const ForwardKernels& K, 
   }
   if (patch < 0 ? !D.any_fft : D.plans[patch].mat != 0) return FCSD_OK;
   a.fft_only = 1;
-  return launch_tileset(s, D.ps[fields - 1], K.fft, a, patch);
+  return launch_tileset(s, D.ps[fields == 4 ? 2 : fields - 1], K.fft, a, patch);
 }
 
 fcsd_status check_set(fcsd_ctx* ctx, const fcsd_set* s, int64_t plane) {
@@ -867,6 +868,16 @@ bool pick_two_rounds(const DirPlan& D) {
   return one.estimate > 0.0 && two.estimate > 0.0 && 2.0 * two.estimate < 0.9 * 4.0 * one.estimate;
 }
 
+// The fused q2 pass keeps all eight H fields in LDS (k_passB4) when that is
+// estimated faster on an untuned set: a half-filled round and a full one on the
+// tiles of four complex lines per grid line, counted as one and a half full
+// ones, take less than four fifths of three on those of two (its epilogue
+// holds four points' registers and stores all of H first).
+bool pick_wide_b(const fcsd_set* s) {
+  const TileSet &two = s->dir[1].ps[1], &four = s->dir[1].ps[2];
+  return s->wide_ok && two.estimate > 0.0 && four.estimate > 0.0 && 1.5 * four.estimate < 0.8 * 3.0 * two.estimate;
+}
+
 // Task queue of the persistent stage kernel from the current tile sets:
 // every A task (q1 tiles in launch order), then the B tasks (q2 tiles) patch by patch in the order in which the
 // patches' last A tasks stand in the queue, then the C tasks (q1 tiles)
@@ -1087,6 +1098,7 @@ extern "C" fcsd_status fcsd_set_create(fcsd_ctx* ctx, int npatch, const fcsd_pat
     // the wide fused q2 pass (four complex lines per grid line) is optional
     s->wide_ok = s->dir[1].ts[2].lds <= (size_t)maxlds;
     s->a_wide = pick_a_wide(s.get());
+    s->b_wide = pick_wide_b(s.get());
     for (auto& D : s->dir) D.two_rounds = pick_two_rounds(D);
   }
   // per-patch descriptors and point chunks
@@ -1292,6 +1304,7 @@ extern "C" fcsd_status fcsd_set_tune(fcsd_set* s, const int lds_budget[3], const
   if ((r = build_stage_tasks(s))) return r;
   s->wide_ok = s->dir[1].ts[2].lds <= (size_t)maxlds;
   s->a_wide = pick_a_wide(s);
+  s->b_wide = pick_wide_b(s);
   for (auto& D : s->dir) D.two_rounds = pick_two_rounds(D);
   if ((s->schedule == FCSD_SCHED_PERSISTENT && !s->persistent_ok) ||
       (s->schedule == FCSD_SCHED_FUSED_WIDE && !s->wide_ok))
@@ -1635,7 +1648,11 @@ fcsd_status rhs_passes(fcsd_ctx* ctx, const fcsd_set* s, const float* u, const f
       if ((st = launch_forward(s, 2, ForwardKernels{{k_mat_B<MatSmall, false>, k_mat_B<MatLarge, false>}, k_passB1}, b, patch, 2))) return st;
   }
   if (fuse) {
-    if ((st = launch_forward(s, 2, ForwardKernels{{k_mat_B<MatSmall, true>, k_mat_B<MatLarge, true>}, k_passB}, b, patch, 2))) return st;
+    if ((st = launch_forward(s, 2,
+                             ForwardKernels{{k_mat_B<MatSmall, true>, k_mat_B<MatLarge, true>},
+                                            s->b_wide ? k_passB4 : k_passB},
+                             b, patch, s->b_wide ? 4 : 2)))
+      return st;
   } else if (passes & 4u) {
     if ((st = launch_forward(s, 2, ForwardKernels{{k_mat_B2<MatSmall>, k_mat_B2<MatLarge>}, k_passB2}, a, patch))) return st;
   }
