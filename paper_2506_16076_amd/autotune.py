@@ -131,6 +131,14 @@ def autotune(s, u, metric, mu, ref, gamma=1.4, dt=None, budgets=DEFAULT_BUDGETS,
     ms, sched, bud, thr, order = min(stage, key=lambda r: r[0])
     s.tune(bud, thr, order)
     s.set_schedule(sched)
+    if sched != 1 and 1 in schedules:
+        # sets without a persistent (or wide) form run fused under its name
+        s.set_schedule(1)
+        fused_ms = time_stage(s, bufs, reps)
+        if fused_ms <= 1.02 * ms:
+            ms, sched = fused_ms, 1
+        else:
+            s.set_schedule(sched)
     names = ["split", "fused", "persistent", "fused_wide"]
     return {"budgets": bud, "threads": thr, "order": "xcd" if order else "lpt", "schedule": names[sched],
             "stage_ms": ms,
