@@ -131,7 +131,8 @@ enum {
  * compute unit; larger workgroups put more threads on each line.  (The
  * passes of lines whose derivative runs as a matrix product take a fixed
  * workgroup size and, of the first or third budget, what tiles of 16 or 32
- * columns need; 80 KB unless tuned.)  A tile
+ * columns need; 80 KB unless tuned.  Until it is tuned, a set's passes run on a
+ * split picked for it, with the results, bit for bit, of the default one.)  A tile
  * whose smallest storage-aligned size exceeds its budget takes more (a
  * launch takes its largest tile's LDS); the q2 tiles of four complex lines
  * per grid line (the reverse mode's q2 pass) share the

@@ -66,7 +66,7 @@ struct MatLarge {  // up to 512 samples
 // (N+1)/2, else slot N-1-i of the second; so do the results.  The split
 // operands of eight pairs take the eight places of their slots: the row pair's
 // first row the hi halves, the second the lo halves.  Then two arrays of
-// column maxima (this round's and the next) and one word per column for the
+// column maxima (of these four fields and of the next) and one word per column for the
 // first tail difference of an odd line, whose place its middle sample holds.
 // The FP64 rows of the tail differences come last.
 __host__ __device__ __forceinline__ size_t mat_lds_bytes(int ks, int ncp, int C, int d) {
@@ -75,7 +75,7 @@ __host__ __device__ __forceinline__ size_t mat_lds_bytes(int ks, int ncp, int C,
 
 struct MatCtx {
   unsigned* z;
-  unsigned* cmax;  // [2][ncp]: bits of each column's largest magnitude, this round and the next
+  unsigned* cmax;  // [2][ncp]: bits of each column's largest magnitude, these four fields' and the next
   float* side;     // [ncp]
   double* dq;      // [C + 1][2 d]
   int ncp, lgc;    // columns (16 or 32) and their log2: 4 fields x (ncp / 4) lines, column f ncp/4 + line
