@@ -20,11 +20,21 @@
 // Operands: v = hi + lo, hi = fp16(v), lo = fp16(v - hi), 22-23 significant
 // bits; hi hi + lo hi + hi lo of every pair are summed in FP32 accumulators of
 // the 16x16x32 products (lo lo is below 2^-22 of a term).  A column is scaled
-// by a power of two from its largest sample (and tail difference) into the top
-// of the fp16 range, the table once per plan, so lo needs no scale of its own:
-// it rounds to zero only below 2^-40 of the largest value.  Against 64 bits
-// the derivative is nearer than the FP32 transform's: about 1.1e-7 of its norm
-// against 2e-7 on smooth lines, 3e-6 against 3e-5 on noise.
+// by a power of two from its largest operand xe, xo (the tail's among them)
+// into the top of the fp16 range, the table once per plan, so lo needs no scale
+// of its own: it rounds to zero only below 2^-39 of the largest operand.  (A
+// scale from the largest sample loses as many of these bits as the sample is
+// larger than its differences.)
+// Error against 64 bits, relative to the derivative's L2 norm (lines of 48 ..
+// 512 samples, d = 2 and 5), products and FP32 transform:
+//   1.4 (1 + a sin), a = 1 .. 1e-3:  1.2e-7 .. 2.0e-7   1.5e-7 .. 3.0e-7
+//   a = 1e-5, 1e-6, d = 2:           0.9e-7 .. 1.5e-7   1.5e-7 .. 4.5e-7
+//   a = 1e-5, 1e-6, d = 5:           3e-7 .. 4e-6       1.5e-6 .. 3e-5
+//   noise, d = 2:                    1.2e-7 .. 2.1e-7   1.4e-7 .. 1.6e-7
+//   noise, d = 5:                    2e-6 .. 7e-6       2e-5 .. 4e-5
+// (noise with d = 2 on lines from 256 samples on is the one kind where the
+// transform is nearer: the products' running sums are rounded once a block of
+// 32 pairs and partial product.)
 //
 // What bounds it: per value L multiply-adds times three partial products, 0.2
 // ms per 15.8 M point stage at the dense fp16 rate, and the table, streamed
@@ -65,22 +75,22 @@ struct MatLarge {  // up to 512 samples
 // distinct banks).  Samples f_i take slot i of the first half, i < Nh =
 // (N+1)/2, else slot N-1-i of the second; so do the results.  The split
 // operands of eight pairs take the eight places of their slots: the row pair's
-// first row the hi halves, the second the lo halves.  Then two arrays of
-// column maxima (of these four fields and of the next) and one word per column for the
-// first tail difference of an odd line, whose place its middle sample holds.
-// The FP64 rows of the tail differences come last.
+// first row the hi halves, the second the lo halves.  Then the column maxima
+// and one word per column for the first tail difference of an odd line, whose
+// place its middle sample holds.  The FP64 rows of the tail differences come
+// last.
 __host__ __device__ __forceinline__ size_t mat_lds_bytes(int ks, int ncp, int C, int d) {
-  return 4 * ((size_t)16 * ks * 4 * ncp + 4 * (size_t)ncp) + 16 * (size_t)(C ? C + 1 : 0) * d;
+  return 4 * ((size_t)16 * ks * 4 * ncp + 2 * (size_t)ncp) + 16 * (size_t)(C ? C + 1 : 0) * d;
 }
 
 struct MatCtx {
   unsigned* z;
-  unsigned* cmax;  // [2][ncp]: bits of each column's largest magnitude, these four fields' and the next
+  unsigned* cmax;  // [ncp]: bits of each column's largest operand
   float* side;     // [ncp]
   double* dq;      // [C + 1][2 d]
   int ncp, lgc;    // columns (16 or 32) and their log2: 4 fields x (ncp / 4) lines, column f ncp/4 + line
   int ldw, hs;     // row stride, offset of the second half
-  int KO, N, Nh, Ni, Pt, round;
+  int KO, N, Nh, Ni, Pt;
 
   __device__ __forceinline__ int odd_row(int row) const { return ncp > 16 ? 4 * (row & 1) : 0; }
   // word of slot n of line `line`, field 0 (field f: f ncp further)
@@ -109,14 +119,12 @@ __device__ __forceinline__ MatCtx mat_setup(unsigned* lds, const PassArgs& a, co
   X.KO = 4 * P.mks;
   X.hs = 2 * X.KO * X.ldw;
   X.cmax = lds + 2 * X.hs;
-  X.side = lds_f(X.cmax + 2 * ncp);
+  X.side = lds_f(X.cmax + ncp);
   X.N = P.N;
   X.Nh = (P.N + 1) >> 1;
   X.Ni = P.N >> 1;
   X.Pt = (P.C + 2) >> 1;
-  X.round = 0;
-  X.dq = reinterpret_cast<double*>(X.side + 2 * ncp);
-  for (int c = threadIdx.x; c < 2 * ncp; c += blockDim.x) X.cmax[c] = 0u;
+  X.dq = reinterpret_cast<double*>(X.side + ncp);
   if (!P.periodic)
     for (int i = threadIdx.x; i < (P.C + 1) * 2 * a.d; i += blockDim.x) X.dq[i] = a.dq[P.dq + i];
   return X;
@@ -193,25 +201,11 @@ __device__ __forceinline__ void mat_walk(const MatCtx& X, const MatThread& M, Pr
   }
 }
 
-// Enter a thread's largest magnitudes of four fields of its line in the column
-// maxima.
-__device__ __forceinline__ void mat_max4(const MatCtx& X, const MatThread& M, float m0, float m1, float m2,
-                                         float m3) {
-  if (M.stop == 0) return;
-  unsigned* cm = X.cmax + (X.round & 1) * X.ncp + M.line;
-  const int q = X.ncp >> 2;
-  atomicMax(cm, __float_as_uint(m0));
-  atomicMax(cm + q, __float_as_uint(m1));
-  atomicMax(cm + 2 * q, __float_as_uint(m2));
-  atomicMax(cm + 3 * q, __float_as_uint(m3));
-}
-
 // Load four fields of the tile (A0 .. A3 at its first stored element) into the
-// sample places, and their column maxima.
+// sample places.
 template <class CLS>
 __device__ __forceinline__ void mat_load4(const MatCtx& X, const MatThread& M, const float* A0, const float* A1,
                                           const float* A2, const float* A3) {
-  float m0 = 0.f, m1 = 0.f, m2 = 0.f, m3 = 0.f;
   float* z = lds_f(X.z);
   const int ncp = X.ncp;
   mat_walk<CLS::load>(
@@ -222,21 +216,15 @@ __device__ __forceinline__ void mat_load4(const MatCtx& X, const MatThread& M, c
         p[ncp] = v.y;
         p[2 * ncp] = v.z;
         p[3 * ncp] = v.w;
-        m0 = fmaxf(m0, fabsf(v.x));
-        m1 = fmaxf(m1, fabsf(v.y));
-        m2 = fmaxf(m2, fabsf(v.z));
-        m3 = fmaxf(m3, fabsf(v.w));
       });
-  mat_max4(X, M, m0, m1, m2, m3);
 }
 
-// Exponent s of a column's scale 2^s: |x_n +- x_n'| <= 4 x the column's
-// largest sample (the tail's differences are entered at half their size),
-// which 2^s takes to at most 2^15.  A column with an infinity or NaN stays
-// unscaled (its results are not finite either way).
+// Exponent s of a column's scale 2^s, which takes its largest operand below
+// 2^15.  A column with an infinity or NaN stays unscaled (its results are not
+// finite either way).
 __device__ __forceinline__ int mat_scale(unsigned bits) {
   const int E = (int)(bits >> 23);
-  return E == 255 ? 0 : min(139 - E, 126);
+  return E == 255 ? 0 : min(141 - E, 126);
 }
 
 // The fp16 halves of two values scaled by sc (a power of two): hi, and what it
@@ -331,7 +319,7 @@ __device__ __forceinline__ void mat_product(const MatCtx& X, const PlanDev& P, c
   if (on) mat_gemm<TR, TC, D>(mt + P.mt, P.mks, rb0, RB, c0, X, acc);
   __syncthreads();  // every operand has been read: the results take their places
   if (on) {
-    const unsigned* cm = X.cmax + (X.round & 1) * X.ncp;
+    const unsigned* cm = X.cmax;
     float* z = lds_f(X.z);
 #pragma unroll
     for (int c = 0; c < TC; ++c) {
@@ -376,21 +364,23 @@ __device__ __forceinline__ void mat_tail(const MatCtx& X, int C, int d, int c, i
     else
       o[0] = xa;
     o[X.hs] = xb;
-    atomicMax(X.cmax + (X.round & 1) * X.ncp + c, __float_as_uint(0.5f * fmaxf(fabsf(xa), fabsf(xb))));
+    // (the larger of |xe| and |xo|)
+    atomicMax(X.cmax + c, __float_as_uint(fabsf(xa) + fabsf(xb)));
   }
 }
 
-// Derivative of every column of the tile: samples and column maxima are in
-// LDS (stored by this thread block, no barrier since); on return the
-// derivatives are in the samples' places, after a barrier.
+// Derivative of every column of the tile: the samples are in LDS (stored by
+// this thread block, no barrier since); on return the derivatives are in the
+// samples' places, after a barrier.
 template <class CLS>
-__device__ __forceinline__ void mat_apply(MatCtx& X, const PlanDev& P, const uint4* __restrict__ mt, int d) {
+__device__ __forceinline__ void mat_apply(const MatCtx& X, const PlanDev& P, const uint4* __restrict__ mt, int d) {
   const int ncp = X.ncp, ldw = X.ldw, hs = X.hs, Ni = X.Ni;
-  unsigned* cm = X.cmax + (X.round & 1) * ncp;
+  unsigned* cm = X.cmax;
   constexpr int T = CLS::threads;
-  __syncthreads();
   // the thread's column, its octets of pairs k0, k0 + dk, ...
   const int tid = mat_tid(), c = tid & (ncp - 1), k0 = tid >> X.lgc, dk = T >> X.lgc;
+  if (tid < ncp) cm[tid] = 0u;  // (its last readers are behind a barrier)
+  __syncthreads();
   float* z = lds_f(X.z);
   // tail differences
   if (P.periodic) {
@@ -402,7 +392,7 @@ __device__ __forceinline__ void mat_apply(MatCtx& X, const PlanDev& P, const uin
       else
         o[0] = x;
       o[hs] = 0.f;
-      atomicMax(cm + c, __float_as_uint(0.5f * fabsf(x)));
+      atomicMax(cm + c, __float_as_uint(fabsf(x)));
     }
   } else if (d == 5) {
     mat_tail<5>(X, P.C, d, c, k0, dk);
@@ -411,7 +401,9 @@ __device__ __forceinline__ void mat_apply(MatCtx& X, const PlanDev& P, const uin
   } else {
     mat_tail<0>(X, P.C, d, c, k0, dk);
   }
-  // sums and differences of the pairs of the thread's octets, in registers
+  // sums and differences of the pairs of the thread's octets, in registers,
+  // and their largest
+  float big = 0.f;
   float xe[CLS::items][8], xo[CLS::items][8];
   float* zc0 = z + 4 * c;                       // even rows
   float* zc1 = z + ldw + 4 * (c ^ X.odd_row(1));  // odd rows
@@ -443,8 +435,18 @@ __device__ __forceinline__ void mat_apply(MatCtx& X, const PlanDev& P, const uin
         xe[i][t] = xa + xb;
         xo[i][t] = xa - xb;
       }
+      // (pairs from Ni on are the tail's)
+      if (8 * k + 8 <= Ni) {
+#pragma unroll
+        for (int t = 0; t < 8; ++t) big = fmaxf(fmaxf(big, fabsf(xe[i][t])), fabsf(xo[i][t]));
+      } else {
+#pragma unroll
+        for (int t = 0; t < 7; ++t)
+          if (8 * k + t < Ni) big = fmaxf(fmaxf(big, fabsf(xe[i][t])), fabsf(xo[i][t]));
+      }
     }
   }
+  atomicMax(cm + c, __float_as_uint(big));
   __syncthreads();
   // the tail's pairs, scale and split in place
   const float sc = __uint_as_float((unsigned)(mat_scale(cm[c]) + 127) << 23);
@@ -478,7 +480,6 @@ __device__ __forceinline__ void mat_apply(MatCtx& X, const PlanDev& P, const uin
       *reinterpret_cast<uint4*>(zc1 + o + hs) = make_uint4(ol[0], ol[1], ol[2], ol[3]);
     }
   }
-  if (tid < ncp) X.cmax[((X.round + 1) & 1) * ncp + tid] = 0u;
   __syncthreads();
   // row blocks per wave
   constexpr int W = CLS::threads / 64, D = CLS::ahead;
@@ -497,7 +498,6 @@ __device__ __forceinline__ void mat_apply(MatCtx& X, const PlanDev& P, const uin
     else if constexpr (CLS::rows > 2)
       mat_product<4, 2, D>(X, P, mt);
   }
-  X.round++;
   __syncthreads();
 }
 
@@ -577,7 +577,7 @@ __global__ void __launch_bounds__(256) k_mat_table(const MatTab* tabs, const dou
 template <class CLS, int DIR>
 __device__ __forceinline__ void mat_diff_tile(const PassArgs& a, const TileDev& T, unsigned* lds) {
   const PlanDev P = a.plans[T.plan];
-  MatCtx X = mat_setup(lds, a, P, T.ld);
+  const MatCtx X = mat_setup(lds, a, P, T.ld);
   const MatThread M = mat_thread<DIR>(X, P, T.nl);
   const long long base = P.off + tile_first<DIR>(T.line0, P.nb1, P.n1), pl = a.plane;
   __syncthreads();
@@ -610,7 +610,7 @@ __device__ __forceinline__ void mat_diff_tile(const PassArgs& a, const TileDev& 
 template <class CLS, bool FUSED>
 __device__ __forceinline__ void mat_B_tile(const PassArgs& a, const TileDev& T, unsigned* lds) {
   const PlanDev P = a.plans[T.plan];
-  MatCtx X = mat_setup(lds, a, P, T.ld);
+  const MatCtx X = mat_setup(lds, a, P, T.ld);
   const MatThread M = mat_thread<2>(X, P, T.nl);
   const long long base = P.off + tile_first<2>(T.line0, P.nb1, P.n1), pl = a.plane;
   const int flux = a.mode, ncp = X.ncp;
@@ -624,7 +624,6 @@ __device__ __forceinline__ void mat_B_tile(const PassArgs& a, const TileDev& T, 
   const HSrc hs = h_sources(a, base, flux);
   float* H = a.H + base;
   float* d2o = a.d2out ? a.d2out + base : nullptr;
-  float m0 = 0.f, m1 = 0.f, m2 = 0.f, m3 = 0.f;
   mat_walk<CLS::epiH>(
       X, M, [&](unsigned g) { return load_H4_inputs(hs, g); },
       [&](unsigned g, int w, const HIn4& q) {
@@ -661,14 +660,9 @@ __device__ __forceinline__ void mat_B_tile(const PassArgs& a, const TileDev& T, 
           p[ncp] = h[1];
           p[2 * ncp] = h[2];
           p[3 * ncp] = h[3];
-          m0 = fmaxf(m0, fabsf(h[0]));
-          m1 = fmaxf(m1, fabsf(h[1]));
-          m2 = fmaxf(m2, fabsf(h[2]));
-          m3 = fmaxf(m3, fabsf(h[3]));
         }
       });
   if (!FUSED) return;
-  mat_max4(X, M, m0, m1, m2, m3);
   const float* m2x = a.metric + 2 * pl + base;
   const float* m2y = a.metric + 3 * pl + base;
   float* r2 = a.r2 + base;
@@ -679,7 +673,7 @@ __device__ __forceinline__ void mat_B_tile(const PassArgs& a, const TileDev& T, 
     }
     mat_apply<CLS>(X, P, a.mt, a.d);
     float* ra = r2 + (2 * half) * pl;
-    mat_walk<8>(
+    mat_walk<6>(
         X, M, [&](unsigned g) { return make_float2(at(m2x, g), at(m2y, g)); },
         [&](unsigned g, int w, float2 m) {
           const float* p = z + w;
@@ -694,7 +688,7 @@ __device__ __forceinline__ void mat_B_tile(const PassArgs& a, const TileDev& T, 
 template <class CLS>
 __device__ __forceinline__ void mat_B2_tile(const PassArgs& a, const TileDev& T, unsigned* lds) {
   const PlanDev P = a.plans[T.plan];
-  MatCtx X = mat_setup(lds, a, P, T.ld);
+  const MatCtx X = mat_setup(lds, a, P, T.ld);
   const MatThread M = mat_thread<2>(X, P, T.nl);
   const long long base = P.off + tile_first<2>(T.line0, P.nb1, P.n1), pl = a.plane;
   const int ncp = X.ncp;
@@ -724,7 +718,7 @@ __device__ __forceinline__ void mat_B2_tile(const PassArgs& a, const TileDev& T,
 template <class CLS>
 __device__ __forceinline__ void mat_C_tile(const PassArgs& a, const TileDev& T, unsigned* lds) {
   const PlanDev P = a.plans[T.plan];
-  MatCtx X = mat_setup(lds, a, P, T.ld);
+  const MatCtx X = mat_setup(lds, a, P, T.ld);
   const MatThread M = mat_thread<1>(X, P, T.nl);
   const long long base = P.off + tile_first<1>(T.line0, P.nb1, P.n1), pl = a.plane;
   const int ncp = X.ncp;

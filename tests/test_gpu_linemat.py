@@ -132,3 +132,53 @@ def test_matrix_columns_keep_apart(env):
     assert np.all(got[3] == 0)
     assert not np.isfinite(got[4]).any() and not np.isfinite(got[5]).any()
     s.close()
+
+
+def operand_norm(x, d, C):
+    """Norm of the products' terms Me xe, Mo xo of lines x over that of their
+    sum, the derivative: what the terms' independent rounding errors are
+    relative to."""
+    M, N = x.shape
+    L = N + C
+    m, k = np.arange(L), np.arange(1, (L - 1) // 2 + 1)
+    kappa = np.cos(2 * np.pi * (np.outer(2 * m - 1, k) % (2 * L)) / (2 * L)) @ (
+        2 * np.pi * k * (N - 1) / L / np.sin(np.pi * k / L)) / L
+    ext = fcgram.extend(x, fcgram.continuation_matrix(d, C))
+    dx = np.roll(ext, -1, 1) - ext
+    n = np.arange(L)
+    nm = (N - 2 - n) % L
+    a = n[n <= nm]
+    b = nm[a]
+    own = a == b
+    K = kappa[(np.arange(N)[:, None] - n) % L]
+    Ka, Kb = K[:(N + 1) // 2][:, a], np.where(own, K[:(N + 1) // 2][:, a], K[:(N + 1) // 2][:, b])
+    xa, xb = dx[:, a], np.where(own, 0, dx[:, b])
+    terms = ((Ka + Kb) / 2) ** 2 @ ((xa + xb) ** 2).T + ((Ka - Kb) / 2) ** 2 @ ((xa - xb) ** 2).T
+    return np.sqrt(2 * terms.sum()) / np.linalg.norm(dx @ K.T)
+
+
+@pytest.mark.parametrize("d", [2, 5])
+@pytest.mark.parametrize("N", [48, 101, 256, 512])
+@pytest.mark.parametrize("amp", [1e-5, 1e-6, 3e-7])
+def test_nearly_uniform_lines(env, d, N, amp):
+    """Lines 1.4 (1 + amp sin): the differences are far below the samples, and
+    keep their bits.  Both operands of a term carry a relative rounding of at
+    most 2^-22 and the dropped product is as small; at most 36 roundings of
+    2^-24 of the FP32 sums, of independent sign: (2^-22 + 6 2^-24) of the norm
+    of the terms (no less than the derivative's) in the L2 norm."""
+    api, ctx, torch = env
+    M, C = 48, 27
+    rng = np.random.default_rng(11)
+    x = np.linspace(0, 1, N)
+    f = (1.4 * (1 + amp * np.sin(2 * np.pi * rng.uniform(.3, 2, (M, 1)) * x + rng.uniform(0, 6, (M, 1))))).astype(
+        np.float32)
+    s, off, plane = make(api, ctx, [(N, M)], d, C, 0)
+    to = torch.zeros(plane, device="cuda:0")
+    api.fc_diff(s, 1, torch.from_numpy(f.reshape(-1)).cuda(), to, 1)
+    got = to.cpu().numpy().reshape(M, N).astype(np.float64)
+    want = fcgram.diff_lines(f.astype(np.float64), d, C)
+    err = np.linalg.norm(got - want) / np.linalg.norm(want)
+    tol = (2.0 ** -22 + 6 * 2.0 ** -24) * max(1.0, operand_norm(f.astype(np.float64), d, C))
+    print("d", d, "N", N, "amp", amp, "rel L2", err, "bar", tol, flush=True)
+    assert err <= tol
+    s.close()
