@@ -173,6 +173,17 @@ enum {
  * bit 0 of the word fcsd_stage_errors reads.  Synchronises the context's
  * stream and drops captured step graphs. */
 fcsd_status fcsd_set_schedule(fcsd_set* set, int schedule);
+/* What a set's line passes run as under its current tuning and schedule (a
+ * report for tuning and tests; changes nothing). */
+typedef struct fcsd_forms {
+  int32_t schedule;      /* FCSD_SCHED_*: what a stage of the whole set runs (sets with walls: fused or split) */
+  int32_t products[2];   /* patches whose q1, q2 derivatives run as matrix products */
+  int32_t transforms[2]; /* patches whose q1, q2 derivatives run as transforms */
+  int32_t a_two_lines;   /* transforms of pass A: tiles of two complex lines per grid line */
+  int32_t b_four_lines;  /* transforms of the fused q2 pass: all eight H fields of a tile in LDS */
+  int32_t two_rounds[2]; /* transforms of four components along q1, q2 (pass C, transposes): two rounds, not four */
+} fcsd_forms;
+fcsd_status fcsd_set_forms(const fcsd_set* set, fcsd_forms* forms);
 /* Read and clear the set's device error word (blocking read).  Bit 0: a
  * persistent stage's dependency wait gave up.  Bit 1: the network weights
  * of a sdnn_infer call (also inside fcsd_step) let the operands of its

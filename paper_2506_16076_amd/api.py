@@ -163,6 +163,18 @@ class PatchSet:
         self.ctx.check(lib().fcsd_set_schedule(self.h, int(schedule)), "fcsd_set_schedule")
         self.schedule = int(schedule)
 
+    def forms(self) -> dict:
+        """What the set's line passes run as under its current tuning and
+        schedule (fcsd_set_forms): "schedule" that a whole-set stage runs,
+        patches per direction whose lines run as "products" and as
+        "transforms", and the variants of the transform passes."""
+        from ._lib import Forms
+        f = Forms()
+        self.ctx.check(lib().fcsd_set_forms(self.h, ctypes.byref(f)), "fcsd_set_forms")
+        return {"schedule": f.schedule, "products": tuple(f.products), "transforms": tuple(f.transforms),
+                "a_two_lines": bool(f.a_two_lines), "b_four_lines": bool(f.b_four_lines),
+                "two_rounds": tuple(bool(v) for v in f.two_rounds)}
+
     def stage_errors(self) -> int:
         """Read and clear the set's device error word (bit 0: a persistent
         stage's dependency wait gave up; bit 1: network weights that can take

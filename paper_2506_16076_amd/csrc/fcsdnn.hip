@@ -1332,6 +1332,21 @@ extern "C" fcsd_status fcsd_set_schedule(fcsd_set* s, int schedule) {
   return FCSD_OK;
 }
 
+extern "C" fcsd_status fcsd_set_forms(const fcsd_set* s, fcsd_forms* f) {
+  if (!s || !f) return FCSD_EINVAL;
+  memset(f, 0, sizeof(*f));
+  f->schedule = s->schedule;
+  if (s->schedule == FCSD_SCHED_FUSED_WIDE || (s->schedule == FCSD_SCHED_PERSISTENT && s->stage_grid == 0))
+    f->schedule = FCSD_SCHED_FUSED;
+  for (int dir = 0; dir < 2; ++dir) {
+    for (const PlanDev& P : s->dir[dir].plans) ++(P.mat ? f->products : f->transforms)[dir];
+    f->two_rounds[dir] = s->dir[dir].two_rounds;
+  }
+  f->a_two_lines = s->a_wide;
+  f->b_four_lines = s->b_wide;
+  return FCSD_OK;
+}
+
 extern "C" fcsd_status fcsd_stage_errors(fcsd_set* s, int32_t* flags) {
   if (!s || !flags) return FCSD_EINVAL;
   fcsd_ctx* ctx = s->ctx;

@@ -89,3 +89,56 @@ def test_untuned_split_changes_no_bit_of_the_reverse(env, name, layout):
         s.close()
     for a, b in zip(*outs):
         assert np.array_equal(a, b)
+
+
+# sets of transforms -> the variants that their untuned split takes
+FORMS = {
+    "few short lines": dict(transforms=(16, 16), a_two_lines=True, b_four_lines=True, two_rounds=(True, True)),
+    "many patches, d = 2": dict(transforms=(64, 64), a_two_lines=True, b_four_lines=False, two_rounds=(True, True)),
+    "one small patch": dict(products=(1, 1), transforms=(0, 0)),
+    "uneven": dict(products=(9, 9), transforms=(0, 0)),
+}
+
+
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("name", list(FORMS))
+def test_variants_of_the_untuned_split(env, name, layout):
+    """The cases that the tests above compare bit for bit do run the variants
+    against their one-line forms: the untuned sets the former, the tuned sets
+    the latter."""
+    api, ctx, torch = env
+    s = api.PatchSet.from_layout(ctx, CASES[name]().ps, layout)
+    f = s.forms()
+    assert {k: f[k] for k in FORMS[name]} == FORMS[name]
+    s.tune(65536, 256)
+    f = s.forms()
+    assert not f["b_four_lines"] and f["two_rounds"] == (False, False)
+    s.close()
+
+
+@pytest.mark.parametrize("layout", [0, 1])
+def test_untuned_split_changes_no_bit_of_the_reverse_of_long_lines(env, layout):
+    """As for short lines; in blocked storage four complex lines per grid line
+    exceed the LDS, so the reverse runs its narrower q2 pass."""
+    api, ctx, torch = env
+    ps = synth.unit_square(700, C=28)      # 728 = 2^3 7 13
+    rng = np.random.default_rng(4)
+    u0 = synth._f32(synth.square_state(ps, rng), ps)
+    bar = rng.standard_normal((4, ps.plane)).astype(np.float32)
+    outs = []
+    for tune in (None, (65536, 256)):
+        s = api.PatchSet.from_layout(ctx, ps, layout)
+        assert s.forms()["transforms"] == (1, 1)
+        if tune:
+            s.tune(*tune)
+        u, metric, rb = s.to_device(u0), s.to_device(ps.metric), s.to_device(bar)
+        mu = s.to_device(np.full((1, ps.plane), 1e-3, np.float32))
+        ub, d1, d2 = (torch.zeros_like(u) for _ in range(3))
+        mb = torch.zeros_like(mu)
+        api.fcsd_rhs_adj(s, u, metric, mu, [1.0, 0.0, 0.0, 1.0], 1.4, rb, ub, mb)
+        api.fc_diff_adj(s, 1, rb, d1, 4)
+        api.fc_diff_adj(s, 2, rb, d2, 4)
+        outs.append([s.to_host(t) for t in (ub, d1, d2, mb)])
+        s.close()
+    for a, b in zip(*outs):
+        assert np.array_equal(a, b)
