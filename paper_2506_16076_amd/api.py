@@ -159,7 +159,8 @@ class PatchSet:
         """Launch schedule of a stage's line passes: SCHED_SPLIT (four
         launches), SCHED_FUSED (three: passes B1 and B2 on one q2 tile),
         SCHED_PERSISTENT (one launch per stage taking tiles from a queue) or
-        SCHED_FUSED_WIDE (three)."""
+        SCHED_FUSED_WIDE (three, the q2 pass's transforms on tiles
+        holding all eight H fields)."""
         self.ctx.check(lib().fcsd_set_schedule(self.h, int(schedule)), "fcsd_set_schedule")
         self.schedule = int(schedule)
 

@@ -1336,14 +1336,15 @@ extern "C" fcsd_status fcsd_set_forms(const fcsd_set* s, fcsd_forms* f) {
   if (!s || !f) return FCSD_EINVAL;
   memset(f, 0, sizeof(*f));
   f->schedule = s->schedule;
-  if (s->schedule == FCSD_SCHED_FUSED_WIDE || (s->schedule == FCSD_SCHED_PERSISTENT && s->stage_grid == 0))
+  if ((s->schedule == FCSD_SCHED_FUSED_WIDE && !s->dir[1].any_fft) ||
+      (s->schedule == FCSD_SCHED_PERSISTENT && s->stage_grid == 0))
     f->schedule = FCSD_SCHED_FUSED;
   for (int dir = 0; dir < 2; ++dir) {
     for (const PlanDev& P : s->dir[dir].plans) ++(P.mat ? f->products : f->transforms)[dir];
     f->two_rounds[dir] = s->dir[dir].two_rounds;
   }
   f->a_two_lines = s->a_wide;
-  f->b_four_lines = s->b_wide;
+  f->b_four_lines = s->b_wide || f->schedule == FCSD_SCHED_FUSED_WIDE;
   return FCSD_OK;
 }
 
@@ -1586,7 +1587,11 @@ fcsd_status rhs_passes(fcsd_ctx* ctx, const fcsd_set* s, const float* u, const f
   // passes B1 and B2 in one launch (a whole-set call of the fused or
   // persistent schedule)
   // (bit 4 of passes asks for it whatever the schedule)
-  const bool fuse = patch < 0 && (s->schedule != FCSD_SCHED_SPLIT || (passes & 16u)) && (passes & 6u) == 6u;
+  const bool fuse = patch < 0 && (s->schedule != FCSD_SCHED_SPLIT || (passes & 48u)) && (passes & 6u) == 6u;
+  // its transforms with all eight H fields in LDS: the wide schedule's (bit 5
+  // of passes asks for it), and the fused one's on sets that pick it
+  const bool wide = fuse && s->wide_ok &&
+                    (s->b_wide || (passes & 32u) || (!(passes & 16u) && s->schedule == FCSD_SCHED_FUSED_WIDE));
   const bool persistent =
       fuse && passes == 15u && !walls && s->schedule == FCSD_SCHED_PERSISTENT && s->stage_grid > 0;
   a.out = W.d1e;
@@ -1665,8 +1670,8 @@ fcsd_status rhs_passes(fcsd_ctx* ctx, const fcsd_set* s, const float* u, const f
   if (fuse) {
     if ((st = launch_forward(s, 2,
                              ForwardKernels{{k_mat_B<MatSmall, true>, k_mat_B<MatLarge, true>},
-                                            s->b_wide ? k_passB4 : k_passB},
-                             b, patch, s->b_wide ? 4 : 2)))
+                                            wide ? k_passB4 : k_passB},
+                             b, patch, wide ? 4 : 2)))
       return st;
   } else if (passes & 4u) {
     if ((st = launch_forward(s, 2, ForwardKernels{{k_mat_B2<MatSmall>, k_mat_B2<MatLarge>}, k_passB2}, a, patch))) return st;
@@ -2049,7 +2054,7 @@ extern "C" fcsd_status fcsd_stage_pass(fcsd_ctx* ctx, const fcsd_set* s, int pas
     return fail(ctx, FCSD_EINVAL, "fcsd_stage_pass: q2 tiles of four complex lines per grid line do not fit the LDS");
   if (ws_bytes < ws_bytes_of(s, FCSD_WS_RHS)) return fail(ctx, FCSD_EINVAL, "fcsd_stage_pass: workspace too small");
   return rhs_passes(ctx, s, ui, metric, mu, ref, gamma, mu ? FLUX_FULL : FLUX_INVISCID, MODE_RK, nullptr, stage, u0,
-                    acc, uout, dt_dev, ws, -1, pass >= 4 ? 6u | 16u : 1u << pass);
+                    acc, uout, dt_dev, ws, -1, pass == 4 ? 6u | 16u : (pass == 5 ? 6u | 32u : 1u << pass));
 }
 
 namespace {

@@ -142,3 +142,32 @@ def test_untuned_split_changes_no_bit_of_the_reverse_of_long_lines(env, layout):
         s.close()
     for a, b in zip(*outs):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("split", ["tuned", "untuned"])
+def test_wide_schedule_runs_its_pass(env, split, layout):
+    """The wide schedule keeps all eight H fields of a q2 tile in LDS on sets
+    of transforms, whatever their tuning, with the bits of the fused one; sets
+    of products have one form and report the fused schedule."""
+    api, ctx, torch = env
+    cfg = CASES["many patches, d = 2"]()
+    ps = cfg.ps
+    s = api.PatchSet.from_layout(ctx, ps, layout)
+    if split == "tuned":
+        s.tune(65536, 256)
+    outs = []
+    for sched in (1, 3):
+        s.set_schedule(sched)
+        f = s.forms()
+        assert f["schedule"] == sched and f["b_four_lines"] == (sched == 3)
+        u, metric = s.to_device(cfg.u0), s.to_device(ps.metric)
+        rhs = torch.zeros_like(u)
+        api.fcsd_rhs(s, u, metric, s.to_device(np.full((1, ps.plane), 1e-3, np.float32)), cfg.ref, 1.4, rhs)
+        outs.append(s.to_host(rhs))
+    assert np.array_equal(*outs)
+    s.close()
+    s = api.PatchSet.from_layout(ctx, CASES["uneven"]().ps, layout)
+    s.set_schedule(3)
+    assert s.forms()["schedule"] == 1
+    s.close()
