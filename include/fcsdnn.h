@@ -167,18 +167,18 @@ enum {
  * rounding (the transposes' tail folds sum in a tile-dependent order).
  * The persistent schedule needs the tile sets' LDS plus 16 bytes (the queue
  * slot) to fit the device's LDS per workgroup (budgets of at most 160 KB -
- * 16), else FCSD_EINVAL.  It is used for every stage of sets without wall
- * sides all of whose lines run as matrix products; stages of other sets (on
- * walls the energy rule runs between passes A and B) fall back to the fused
- * schedule.  A dependency
- * wait that gives up (never expected: it would take about a second) sets
+ * 16), else FCSD_EINVAL; every task runs on workgroups of the q1 tile set's
+ * size, or on sets with lines that run as matrix products on theirs.  It is
+ * used for every stage of sets without wall sides; stages of sets with walls
+ * (whose energy rule runs between passes A and B) fall back to the fused
+ * schedule.  A dependency wait that gives up (never expected: it would take about a second) sets
  * bit 0 of the word fcsd_stage_errors reads.  Synchronises the context's
  * stream and drops captured step graphs. */
 fcsd_status fcsd_set_schedule(fcsd_set* set, int schedule);
 /* What a set's line passes run as under its current tuning and schedule (a
  * report for tuning and tests; changes nothing). */
 typedef struct fcsd_forms {
-  int32_t schedule;      /* FCSD_SCHED_*: what a stage of the whole set runs (sets with walls: fused or split) */
+  int32_t schedule;      /* FCSD_SCHED_*: what a viscous stage of the whole set runs */
   int32_t products[2];   /* patches whose q1, q2 derivatives run as matrix products */
   int32_t transforms[2]; /* patches whose q1, q2 derivatives run as transforms */
   int32_t a_two_lines;   /* transforms of pass A: tiles of two complex lines per grid line */

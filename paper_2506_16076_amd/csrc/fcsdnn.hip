@@ -181,8 +181,8 @@ struct fcsd_set {
   int ntasks = 0;
   unsigned* d_ctr = nullptr;              // queue head, 2 npatch counters, then the error word
   unsigned* d_need = nullptr;             // 2 npatch: A tiles, B tiles per patch
-  unsigned stage_grid = 0;                // resident workgroups of the persistent launch (0: it runs fused)
-  bool persistent_ok = false;             // the persistent schedule can be selected
+  unsigned stage_grid = 0;                // resident workgroups of the persistent launch (0: it cannot run)
+  void (*stage_kernel)(StageArgs) = nullptr;
   size_t stage_lds = 0;
   int stage_threads = 0;
   bool wide_ok = false;                   // the q2 tiles of four complex lines per grid line fit the LDS
@@ -879,45 +879,53 @@ bool pick_wide_b(const fcsd_set* s) {
 }
 
 // Task queue of the persistent stage kernel from the current tile sets:
-// every A task (q1 tiles in launch order), then the B tasks (q2 tiles) patch by patch in the order in which the
-// patches' last A tasks stand in the queue, then the C tasks (q1 tiles)
-// patch by patch in the order of the patches' last B tasks, so that the
+// every A task (q1 tiles in launch order, of transforms then of products), then
+// the B tasks (q2 tiles; the transforms' with two complex lines per grid line)
+// patch by patch in the order in which the patches' last A tasks stand in the
+// queue, then the C tasks (q1 tiles) patch by patch in the order of the patches' last B tasks, so that the
 // tasks taken first are the ones whose inputs are done first.  Also the
 // per-patch tile counts, the counters and the launch shape.
 fcsd_status build_stage_tasks(fcsd_set* s) {
   fcsd_ctx* ctx = s->ctx;
   const int np = s->npatch;
   fcsd_status r;
-  const TileSet &TA = s->dir[0].ms, &TB = s->dir[1].ms;
   std::vector<int2> tasks;
   std::vector<unsigned> need(2 * (size_t)np, 0u);
   std::vector<long long> lastA(np, -1), lastB(np, -1);
-  for (size_t i = 0; i < TA.tiles.size(); ++i) {
-    const TileDev& T = TA.tiles[i];
-    if (T.nl == 0) continue;
-    lastA[T.plan] = (long long)tasks.size();
-    ++need[T.plan];
-    tasks.push_back(make_int2(TASK_A, (int)i));
-  }
+  // the tiles of the direction's transforms (f: their tile set) and products
+  size_t lds = 0;
+  auto each_tile = [&](const DirPlan& D, int f, auto&& use) {
+    for (int mat = 0; mat < 2; ++mat) {
+      const TileSet& S = mat ? D.ms : D.ts[f];
+      for (size_t i = 0; i < S.tiles.size(); ++i) {
+        const TileDev& T = S.tiles[i];
+        if (T.nl == 0 || (D.plans[T.plan].mat != 0) != mat) continue;
+        lds = std::max(lds, S.patch_lds[T.plan]);
+        use(T.plan, mat ? (int)TASK_MAT : 0, (int)i);
+      }
+    }
+  };
+  each_tile(s->dir[0], 0, [&](int p, int form, int i) {
+    lastA[p] = (long long)tasks.size();
+    ++need[p];
+    tasks.push_back(make_int2(TASK_A | form, i));
+  });
   auto by_last = [&](const std::vector<long long>& last) {
     std::vector<int> ord(np);
     for (int p = 0; p < np; ++p) ord[p] = p;
     std::stable_sort(ord.begin(), ord.end(), [&](int a, int b) { return last[a] < last[b]; });
     return ord;
   };
-  std::vector<std::vector<int>> tb(np), ta(np);
-  for (size_t i = 0; i < TB.tiles.size(); ++i)
-    if (TB.tiles[i].nl > 0) tb[TB.tiles[i].plan].push_back((int)i);
-  for (size_t i = 0; i < TA.tiles.size(); ++i)
-    if (TA.tiles[i].nl > 0) ta[TA.tiles[i].plan].push_back((int)i);
+  std::vector<std::vector<int2>> tb(np), tc(np);
+  each_tile(s->dir[1], 1, [&](int p, int form, int i) { tb[p].push_back(make_int2(TASK_B | form, i)); });
+  each_tile(s->dir[0], 0, [&](int p, int form, int i) { tc[p].push_back(make_int2(TASK_C | form, i)); });
   for (int p : by_last(lastA))
-    for (int i : tb[p]) {
+    for (const int2& t : tb[p]) {
       lastB[p] = (long long)tasks.size();
       ++need[np + p];
-      tasks.push_back(make_int2(TASK_B, i));
+      tasks.push_back(t);
     }
-  for (int p : by_last(lastB))
-    for (int i : ta[p]) tasks.push_back(make_int2(TASK_C, i));
+  for (int p : by_last(lastB)) tasks.insert(tasks.end(), tc[p].begin(), tc[p].end());
   (void)hipFree(s->d_tasks);
   (void)hipFree(s->d_need);
   s->d_tasks = nullptr;
@@ -929,18 +937,21 @@ fcsd_status build_stage_tasks(fcsd_set* s) {
     HIPCHK(ctx, hipMalloc(&s->d_ctr, words * sizeof(unsigned)));
     HIPCHK(ctx, hipMemset(s->d_ctr, 0, words * sizeof(unsigned)));
   }
-  // launch shape: the larger LDS of the two directions plus the queue slot, as many workgroups as can be resident.  The schedule itself is
-  // accepted when the transform's tiles leave room for the slot.
-  s->stage_threads = MatLarge::threads;
-  s->stage_lds = std::max(TA.lds, TB.lds) + 16;
+  // launch shape: the q1 set's workgroup size (the products' on sets with
+  // products), the largest tile's LDS plus the queue slot, as many workgroups
+  // as can be resident
+  const bool fft = s->dir[0].any_fft || s->dir[1].any_fft;
+  const bool mat = !s->dir[0].ms.tiles.empty() || !s->dir[1].ms.tiles.empty();
+  s->stage_kernel = !mat ? k_stage : fft ? k_stage_mat<true> : k_stage_mat<false>;
+  s->stage_threads = mat ? MatLarge::threads : s->dir[0].ts[0].threads;
+  s->stage_lds = lds + 16;
   s->stage_grid = 0;
   int maxlds = 0, ncu = 0, per_cu = 0;
   HIPCHK(ctx, hipDeviceGetAttribute(&maxlds, hipDeviceAttributeMaxSharedMemoryPerBlock, ctx->device));
-  s->persistent_ok = std::max(s->dir[0].ts[0].lds, s->dir[1].ts[1].lds) + 16 <= (size_t)maxlds;
-  // lines that run as transforms have no persistent form
-  if (s->dir[0].any_fft || s->dir[1].any_fft || s->stage_lds > (size_t)maxlds) return FCSD_OK;
+  if (std::max(s->stage_lds, std::max(s->dir[0].ts[0].lds, s->dir[1].ts[1].lds) + 16) > (size_t)maxlds)
+    return FCSD_OK;  // the persistent schedule cannot run with these tiles
   HIPCHK(ctx, hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, ctx->device));
-  HIPCHK(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_stage, s->stage_threads, s->stage_lds));
+  HIPCHK(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, s->stage_kernel, s->stage_threads, s->stage_lds));
   s->stage_grid = (unsigned)std::max(0, std::min(s->ntasks, per_cu * ncu));
   return FCSD_OK;
 }
@@ -1306,7 +1317,7 @@ extern "C" fcsd_status fcsd_set_tune(fcsd_set* s, const int lds_budget[3], const
   s->a_wide = pick_a_wide(s);
   s->b_wide = pick_wide_b(s);
   for (auto& D : s->dir) D.two_rounds = pick_two_rounds(D);
-  if ((s->schedule == FCSD_SCHED_PERSISTENT && !s->persistent_ok) ||
+  if ((s->schedule == FCSD_SCHED_PERSISTENT && s->stage_grid == 0) ||
       (s->schedule == FCSD_SCHED_FUSED_WIDE && !s->wide_ok))
     s->schedule = FCSD_SCHED_FUSED;
   return rebuild_wall_tiles(s);
@@ -1318,7 +1329,7 @@ extern "C" fcsd_status fcsd_set_schedule(fcsd_set* s, int schedule) {
   if (schedule != FCSD_SCHED_SPLIT && schedule != FCSD_SCHED_FUSED && schedule != FCSD_SCHED_PERSISTENT &&
       schedule != FCSD_SCHED_FUSED_WIDE)
     return fail(ctx, FCSD_EINVAL, "fcsd_set_schedule: unknown schedule");
-  if (schedule == FCSD_SCHED_PERSISTENT && !s->persistent_ok)
+  if (schedule == FCSD_SCHED_PERSISTENT && s->stage_grid == 0)
     return fail(ctx, FCSD_EINVAL,
                 "fcsd_set_schedule: the tile sets leave no room for the persistent kernel's queue slot "
                 "(tune LDS budgets to at most 160 KB - 16)");
@@ -1337,7 +1348,7 @@ extern "C" fcsd_status fcsd_set_forms(const fcsd_set* s, fcsd_forms* f) {
   memset(f, 0, sizeof(*f));
   f->schedule = s->schedule;
   if ((s->schedule == FCSD_SCHED_FUSED_WIDE && !s->dir[1].any_fft) ||
-      (s->schedule == FCSD_SCHED_PERSISTENT && s->stage_grid == 0))
+      (s->schedule == FCSD_SCHED_PERSISTENT && s->nwchunks > 0))
     f->schedule = FCSD_SCHED_FUSED;
   for (int dir = 0; dir < 2; ++dir) {
     for (const PlanDev& P : s->dir[dir].plans) ++(P.mat ? f->products : f->transforms)[dir];
@@ -1592,8 +1603,7 @@ fcsd_status rhs_passes(fcsd_ctx* ctx, const fcsd_set* s, const float* u, const f
   // of passes asks for it), and the fused one's on sets that pick it
   const bool wide = fuse && s->wide_ok &&
                     (s->b_wide || (passes & 32u) || (!(passes & 16u) && s->schedule == FCSD_SCHED_FUSED_WIDE));
-  const bool persistent =
-      fuse && passes == 15u && !walls && s->schedule == FCSD_SCHED_PERSISTENT && s->stage_grid > 0;
+  const bool persistent = fuse && passes == 15u && !walls && s->schedule == FCSD_SCHED_PERSISTENT;
   a.out = W.d1e;
   PassArgs b = a;
   b.plans = s->dir[1].d_plans;
@@ -1616,11 +1626,12 @@ fcsd_status rhs_passes(fcsd_ctx* ctx, const fcsd_set* s, const float* u, const f
     g.A = a;
     g.A.in = u;
     g.A.nf = 4;
-    g.A.tiles = s->dir[0].ms.d_tiles;
     g.B = b;
-    g.B.tiles = s->dir[1].ms.d_tiles;
     g.C = e;
-    g.C.tiles = s->dir[0].ms.d_tiles;
+    g.q1[0] = s->dir[0].ts[0].d_tiles;
+    g.q1[1] = s->dir[0].ms.d_tiles;
+    g.q2[0] = s->dir[1].ts[1].d_tiles;
+    g.q2[1] = s->dir[1].ms.d_tiles;
     g.tasks = s->d_tasks;
     g.ntasks = s->ntasks;
     g.npatch = np;
@@ -1632,7 +1643,7 @@ fcsd_status rhs_passes(fcsd_ctx* ctx, const fcsd_set* s, const float* u, const f
     const long long nw = 1 + 2 * (long long)np;
     hipLaunchKernelGGL(k_fill, dim3(blocks_for(nw)), dim3(kBlock), 0, ctx->stream, (float*)s->d_ctr, 0.0f, nw);
     if ((st = launch_check(ctx, "stage counters"))) return st;
-    hipLaunchKernelGGL(k_stage, dim3(s->stage_grid), dim3(s->stage_threads), s->stage_lds, ctx->stream, g);
+    hipLaunchKernelGGL(s->stage_kernel, dim3(s->stage_grid), dim3(s->stage_threads), s->stage_lds, ctx->stream, g);
     return launch_check(ctx, "persistent stage");
   }
   if (flux == FLUX_INVISCID) {

@@ -811,11 +811,13 @@ __global__ void FCSD_MAT_BOUNDS(CLS) k_mat_C(PassArgs a) {
 // ---------------------------------------------------------------- one launch per stage
 
 // Task kinds of the persistent stage kernel: pass A on a q1 tile, passes
-// B1 + B2 on a q2 tile, pass C on a q1 tile.
-enum { TASK_A = 0, TASK_B = 1, TASK_C = 2 };
+// B1 + B2 on a q2 tile, pass C on a q1 tile; TASK_MAT: a tile of lines that
+// run as matrix products.
+enum { TASK_A = 0, TASK_B = 1, TASK_C = 2, TASK_MAT = 4 };
 
 struct StageArgs {
-  PassArgs A, B, C;         // the passes' arguments (A.tiles, B.tiles: the q1 and q2 tile arrays)
+  PassArgs A, B, C;         // the passes' arguments
+  const TileDev *q1[2], *q2[2];  // tiles of the lines that run as transforms, as products
   const int2* tasks;        // (kind, tile index), in queue order
   int ntasks;
   int npatch;
@@ -840,11 +842,14 @@ constexpr int kSpinLimit = 1 << 24;
 // thread's stores are then complete); a dependent task starts after an
 // acquire poll of that counter.  Phases of different patches overlap, and no
 // workgroup idles at the end of a pass.  The counters start at zero (the
-// host clears them before the launch).
-__global__ void FCSD_MAT_BOUNDS(MatLarge) k_stage(StageArgs s) {
+// host clears them before the launch).  FFT, MAT: the queue holds tiles of
+// transforms, of products.
+template <bool FFT, bool MAT>
+__device__ __forceinline__ void stage_tasks(const StageArgs& s) {
   // the first 16 bytes of the dynamic LDS hold the task index; tiles start after
   int* slot = reinterpret_cast<int*>(lds_z);
-  unsigned* lds = reinterpret_cast<unsigned*>(lds_z) + 4;
+  float2* lds = lds_z + 2;
+  unsigned* mlds = reinterpret_cast<unsigned*>(lds);
   const int np = s.npatch;
   for (;;) {
     __syncthreads();  // the previous task's LDS reads are done; the slot is free
@@ -853,11 +858,13 @@ __global__ void FCSD_MAT_BOUNDS(MatLarge) k_stage(StageArgs s) {
     const int t = slot[0];
     if (t >= s.ntasks) return;
     const int2 k = s.tasks[t];
-    const TileDev T = (k.x == TASK_B ? s.B.tiles : s.A.tiles)[k.y];
+    const int kind = k.x & 3;
+    const bool mat = MAT && (!FFT || (k.x & TASK_MAT));
+    const TileDev T = (kind == TASK_B ? s.q2 : s.q1)[mat][k.y];
     const int p = T.plan;  // one plan per patch and direction
-    if (k.x != TASK_A) {
+    if (kind != TASK_A) {
       if (threadIdx.x == 0) {
-        const int dep = (k.x == TASK_B ? 0 : np) + p;
+        const int dep = (kind == TASK_B ? 0 : np) + p;
         const unsigned need = s.need[dep];
         unsigned* c = s.ctr + 1 + dep;
         int polls = 0;
@@ -871,20 +878,43 @@ __global__ void FCSD_MAT_BOUNDS(MatLarge) k_stage(StageArgs s) {
       }
       __syncthreads();
     }
-    if (k.x == TASK_A) {
-      if (!s.skipA) mat_diff_tile<MatLarge, 1>(s.A, T, lds);
-    } else if (k.x == TASK_B) {
-      mat_B_tile<MatLarge, true>(s.B, T, lds);
-    } else {
-      mat_C_tile<MatLarge>(s.C, T, lds);
+    if constexpr (MAT) {
+      if (mat) {
+        if (kind == TASK_A) {
+          if (!s.skipA) mat_diff_tile<MatLarge, 1>(s.A, T, mlds);
+        } else if (kind == TASK_B) {
+          mat_B_tile<MatLarge, true>(s.B, T, mlds);
+        } else {
+          mat_C_tile<MatLarge>(s.C, T, mlds);
+        }
+      }
     }
-    if (k.x != TASK_C) {
+    if constexpr (FFT) {
+      if (!mat) {
+        if (kind == TASK_A) {
+          if (!s.skipA) dev_diff_tile<1>(s.A, T, lds);
+        } else if (kind == TASK_B) {
+          passB_tile<true>(s.B, T, lds);
+        } else {
+          passC_tile(s.C, T, lds);
+        }
+      }
+    }
+    if (kind != TASK_C) {
       __syncthreads();  // every thread's stores of the task are complete
       if (threadIdx.x == 0)
-        __hip_atomic_fetch_add(s.ctr + 1 + (k.x == TASK_A ? 0 : np) + p, 1u, __ATOMIC_RELEASE,
+        __hip_atomic_fetch_add(s.ctr + 1 + (kind == TASK_A ? 0 : np) + p, 1u, __ATOMIC_RELEASE,
                                __HIP_MEMORY_SCOPE_AGENT);
     }
   }
+}
+
+__global__ void FCSD_LINE_BOUNDS k_stage(StageArgs s) { stage_tasks<true, false>(s); }
+
+// Sets with products: the products' workgroup size for every task.
+template <bool FFT>
+__global__ void FCSD_MAT_BOUNDS(MatLarge) k_stage_mat(StageArgs s) {
+  stage_tasks<FFT, true>(s);
 }
 
 }  // namespace fcsd

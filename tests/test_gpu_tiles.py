@@ -171,3 +171,43 @@ def test_wide_schedule_runs_its_pass(env, split, layout):
     s.set_schedule(3)
     assert s.forms()["schedule"] == 1
     s.close()
+
+
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("name", ["transforms", "products", "both"])
+def test_persistent_schedule_runs_on_every_set(env, name, layout):
+    """One launch per stage on sets of transforms, of products, and of both
+    (lines above 512 points next to short ones, along each direction): the
+    schedule reports itself, its waits never give up, and its right-hand side
+    has the fused schedule's bits, on short and long queues."""
+    api, ctx, torch = env
+    if name == "transforms":
+        ps = CASES["many patches, d = 2"]().ps
+    elif name == "products":
+        ps = CASES["uneven"]().ps
+    else:
+        ps = synth.uneven_sectors(5, 60, 700, 3)
+    n1, n2 = np.asarray(ps.n1), np.asarray(ps.n2)
+    prod = (0, 0) if name == "transforms" else (int((n1 <= 512).sum()), int((n2 <= 512).sum()))
+    rng = np.random.default_rng(8)
+    u0 = synth._f32(synth.mach_state(ps, 3.0, synth.draw_perturbation(rng)), ps)
+    for tune in (None, ((16384, 16384, 24576), (256, 256, 256))):
+        s = api.PatchSet.from_layout(ctx, ps, layout)
+        if tune:
+            s.tune(*tune)
+        f = s.forms()
+        assert f["products"] == prod and f["transforms"] == (ps.npatch - prod[0], ps.npatch - prod[1])
+        u, metric = s.to_device(u0), s.to_device(ps.metric)
+        mu = s.to_device(np.full((1, ps.plane), 1e-3, np.float32))
+        outs = []
+        for sched in (1, 2):
+            s.set_schedule(sched)
+            assert s.forms()["schedule"] == sched
+            rhs = torch.zeros_like(u)
+            api.fcsd_rhs(s, u, metric, mu, [1.4, 3.0, 0.0, 1.0], 1.4, rhs)
+            outs.append(s.to_host(rhs))
+        assert s.stage_errors() == 0
+        assert np.array_equal(*outs)
+        s.close()
+    if name == "both":
+        assert 0 < prod[0] < ps.npatch and 0 < prod[1] < ps.npatch
