@@ -62,22 +62,18 @@ struct PlanDev {
   long long off; // patch offset in a plane
 };
 
-// How many lanes share a line in the transposed operators' fold (fold_pre):
-// what a tile of n grid lines gives workgroups of `threads`, n = first for the
-// tile's grid lines before `last0`, last from there on.  The fold's sums run
-// in an order that depends on it, so it belongs to the set's tuning (its
-// nominal tiles), whatever tiles a pass is launched over.
-struct FoldLanes {
-  int threads, first, last, last0;
-};
-
+// fold[k]: how many lanes share a line in the transposed operators' fold
+// (fold_pre) on 2^k complex lines per grid line.  The fold's sums run in an
+// order that depends on it, so it is what the set's nominal tiles (its tuning)
+// give, whatever tiles a pass is launched over: 2^(bits 8 .. 11) lanes for the
+// tile's grid lines before (bits 0 .. 7), 2^(bits 12 .. 15) from there on (the
+// nominal split's last tile).  The first part is never empty.
 struct TileDev {
   int plan;   // index into the plan array of the direction
   int line0;  // first line of the tile
   int nl;     // lines in the tile
   int ld;     // LDS stride in float2 (odd, >= nl)
-  FoldLanes fold;   // nominal tiles of the same kind
-  FoldLanes fold1;  // those of one complex line per grid line
+  int fold[3], pad;
 };
 
 // Per-thread view of a tile in LDS.  Layout of the dynamic LDS block:
@@ -521,14 +517,13 @@ __device__ __forceinline__ void fold_tail(const LineCtx& X, const PlanDev& P, co
 // (~1e-7 of the line's largest cotangent).  S lanes (a power of two,
 // S * nl <= blockDim) share a line, each summing every S-th sample with the
 // loads of eight samples (four for d > 5) in flight together, and reduce with lane shuffles
-// inside their wave.  S is that of the set's nominal tiles (FoldLanes).  No
+// inside their wave.  S is that of the set's nominal tiles (TileDev).  No
 // barrier: reads positions < N, writes side.  DD >= d bounds the unrolled
 // accumulators.
 template <int DD>
 __device__ __forceinline__ void fold_lines(const LineCtx& X, int N, const float* __restrict__ G, int d, int S,
-                                           int c, bool on) {
+                                           int s, int c, bool on) {
   constexpr int U = DD <= 5 ? 8 : 4;  // samples whose loads are in flight together
-  const int s = threadIdx.x & (S - 1);
   const int cc = on ? c : 0;
   const float2* __restrict__ z = X.z;
   const int ld = X.ld, w = 2 * d;
@@ -575,36 +570,48 @@ __device__ __forceinline__ void fold_lines(const LineCtx& X, int N, const float*
   }
 }
 
-// T: the tile of grid lines, each X.nl / T.nl complex lines of the context
-// (complex line f T.nl + l belongs to grid line l); W: nominal tiles of W
-// complex lines per grid line (1: fold1), 0: of as many as the context's.
-template <int DD>
-__device__ __forceinline__ void fold_pre_t(const LineCtx& X, int N, const float* __restrict__ G, int d,
-                                           const TileDev& T, int W) {
-  const int F = X.nl / T.nl;
-  const FoldLanes Q = W == 1 ? T.fold1 : T.fold;
-  if (W == 0) W = F;
-  for (int part = 0; part < 2; ++part) {
-    const int l0 = part ? Q.last0 : 0, cnt = part ? T.nl - l0 : Q.last0;
-    if (cnt <= 0) continue;
-    int lg = 6;  // S = 2^lg
-    while (((W * (part ? Q.last : Q.first)) << lg) > Q.threads) --lg;
-    const int step = (int)blockDim.x >> lg;
-    for (int m0 = 0; m0 < F * cnt; m0 += step) {
-      const int m = m0 + (int)(threadIdx.x >> lg), f = m / cnt;
-      fold_lines<DD>(X, N, G, d, 1 << lg, f * T.nl + l0 + (m - f * cnt), m < F * cnt);
-    }
+// nl grid lines of F complex lines each (complex line f nl + l belongs to grid
+// line l), lanes: TileDev::fold.  NOM: the tiles are the nominal ones (a tuned
+// set's), so every line has its lanes at once and there is nothing to turn over
+// (the loop costs the reverse passes of 15 .. 17 M points 2 .. 4 %: the q1
+// transpose of the 16 x 4 x 512 x 512 annulus 433 against 410 us).
+template <int DD, bool NOM>
+__device__ __forceinline__ void fold_pre_t(const LineCtx& X, int N, const float* __restrict__ G, int d, int nl, int F,
+                                           int lanes) {
+  if (NOM) {
+    int S = 64;
+    while (S * X.nl > (int)blockDim.x) S >>= 1;
+    const int c = threadIdx.x / S;
+    fold_lines<DD>(X, N, G, d, S, threadIdx.x - c * S, c, c < X.nl);
+    return;
   }
+  int l0 = 0, cnt = lanes & 255, lg = (lanes >> 8) & 15, m0 = 0;
+#pragma unroll 1
+  do {
+    const int m = m0 + (int)(threadIdx.x >> lg);
+    const int f = (F > 1 && m >= cnt) + (F > 2 && m >= 2 * cnt) + (F > 3 && m >= 3 * cnt);
+    fold_lines<DD>(X, N, G, d, 1 << lg, threadIdx.x & ((1 << lg) - 1), l0 + m + f * (nl - cnt), m < F * cnt);
+    m0 += (int)blockDim.x >> lg;
+    if (m0 >= F * cnt) {
+      m0 = 0;
+      l0 += cnt;
+      cnt = nl - l0;
+      lg = lanes >> 12;
+    }
+  } while (l0 < nl);
 }
 
+// The tile T's lines, F (a constant) complex ones per grid line, folded as on
+// nominal tiles of 2^K.
+template <int F, int K, bool NOM>
 __device__ __forceinline__ void fold_pre(const LineCtx& X, int N, const float* __restrict__ G, int d,
-                                         const TileDev& T, int W = 0) {
+                                         const TileDev& T) {
   if (d <= 2)
-    fold_pre_t<2>(X, N, G, d, T, W);
+    fold_pre_t<2, NOM>(X, N, G, d, T.nl, F, T.fold[K]);
   else if (d <= 5)
-    fold_pre_t<5>(X, N, G, d, T, W);
+    fold_pre_t<5, NOM>(X, N, G, d, T.nl, F, T.fold[K]);
   else
-    fold_pre_t<kMaxD>(X, N, G, d, T, W);
+    fold_pre_t<kMaxD, NOM>(X, N, G, d, T.nl, F, T.fold[K]);
 }
 
 // Add the fold that fold_pre left in the side buffer to the end samples
@@ -813,23 +820,18 @@ __device__ __forceinline__ void fft_apply(const LineCtx& X, const PlanDev* __res
   }
 }
 
-// Derivative of the tile in place; the caller has filled positions 0..N-1
-// and synchronised.  ADJ = transpose: the tail fold from the cotangent in
-// FP64 (fold_pre; its reads of positions < N end before difference_adj's
-// first barrier, after which those positions are overwritten), Delta^T,
-// conjugate multipliers, then the fold added to the end samples.
-template <bool ADJ>
-__device__ __forceinline__ void line_derivative(const LineCtx& X, const PlanDev* __restrict__ Pg, const PlanDev& P,
-                                const float* __restrict__ gqp, const double* __restrict__ dqp, int d,
-                                const TileDev& T, int W = 0) {
-  if (!ADJ) {
-    difference_ext(X, P, dqp + P.dq, d);
-  } else {
-    if (!P.periodic) fold_pre(X, P.N, gqp + P.gq, d, T, W);
-    difference_adj(X, P);
-  }
-  fft_apply<ADJ>(X, Pg, P);
-  if (ADJ && !P.periodic) {
+// Transpose of the derivative of the tile in place; the caller has filled
+// positions 0..N-1 and synchronised: the tail fold from the cotangent
+// (fold_pre; its reads of positions < N end before difference_adj's first
+// barrier, after which those positions are overwritten), Delta^T, conjugate
+// multipliers, then the fold added to the end samples.
+template <int F, int K, bool NOM>
+__device__ __forceinline__ void line_derivative_adj(const LineCtx& X, const PlanDev* __restrict__ Pg, const PlanDev& P,
+                                                    const float* __restrict__ gqp, int d, const TileDev& T) {
+  if (!P.periodic) fold_pre<F, K, NOM>(X, P.N, gqp + P.gq, d, T);
+  difference_adj(X, P);
+  fft_apply<true>(X, Pg, P);
+  if (!P.periodic) {
     fold_post(X, P.N, d);
     __syncthreads();
   }

@@ -107,6 +107,7 @@ struct DirPlan {
   std::vector<PlanDev> plans;             // one per patch
   TileSet ts[3];                          // one / two / four complex lines per grid line
   TileSet ps[3];                          // the passes' tiles (ts when tuned, else picked for the set), like ts
+  bool nominal = true;                    // ps is the split of ts
   bool two_rounds = false;                // passes over four components: two rounds on ps[1], not four on ps[0]
   TileSet ms;                             // lines whose derivative runs as a matrix product (linemat.h)
   bool mat_large = false;                 // by the kernels for large lines
@@ -575,11 +576,21 @@ void order_tiles(const std::vector<PlanDev>& plans, TileSet& D, int order, const
   empty.line0 = 0;
   empty.nl = 0;
   empty.ld = 1;
-  empty.fold = empty.fold1 = FoldLanes{kBlock, 1, 1, 0};
+  empty.fold[0] = empty.fold[1] = empty.fold[2] = empty.pad = 0;
   D.tiles.assign(mx * kXcd, empty);
   for (int x = 0; x < kXcd; ++x)
     for (size_t k = 0; k < lst[x].size(); ++k) D.tiles[k * kXcd + x] = lst[x][k];
 }
+
+// Lanes per line of the fold (TileDev::fold) on w complex lines per grid line:
+// workgroups of `threads` over n grid lines give 2^fold_log each, at most a
+// wave's.
+int fold_log(int threads, int n, int w) {
+  int lg = 6;
+  while (lg > 0 && ((w * n) << lg) > threads) --lg;
+  return lg;
+}
+int fold_lanes(int last0, int first, int last) { return last0 | first << 8 | last << 12; }
 
 // (order < 0: the tiles only, not the launch order.)
 void build_tileset(const std::vector<PlanDev>& plans, TileSet& D, size_t budget, int order, int fields, int align,
@@ -613,7 +624,11 @@ void build_tileset(const std::vector<PlanDev>& plans, TileSet& D, size_t budget,
       // of one are worth far more than the conflicts (the q2 tiles of two
       // complex lines per grid line on the longest lines: 83 KB odd, 79 KB even)
       T.ld = (fields * T.nl) | 1;
-      T.fold = T.fold1 = FoldLanes{D.threads, T.nl, T.nl, T.nl};
+      for (int k = 0; k < 3; ++k) {
+        const int lg = fold_log(D.threads, T.nl, 1 << k);
+        T.fold[k] = fold_lanes(T.nl, lg, lg);
+      }
+      T.pad = 0;
       if (per_ld * T.ld + tables > budget && per_ld * (fields * T.nl) + tables <= budget) T.ld = fields * T.nl;
       D.tiles_by_patch.push_back(T);
       plds = std::max(plds, per_ld * T.ld + tables);
@@ -691,15 +706,17 @@ void pick_tiles(DirPlan& D, int f, int order, int align, int d, size_t maxlds) {
   if (!budget) F.threads = 1024;
   build_tileset(D.plans, F, F.budget, order, 1 << f, align, d);
   F.estimate = best;
-  auto lanes_of = [](const TileSet& n, const TileDev& T) {
+  auto lanes_of = [](const TileSet& n, const TileDev& T, int w) {
     const TileDev &first = n.tiles_by_patch[n.patch_begin[T.plan]];
     const TileDev &last = n.tiles_by_patch[n.patch_begin[T.plan + 1] - 1];
-    return FoldLanes{n.threads, first.nl, last.nl, std::min(std::max(last.line0 - T.line0, 0), T.nl)};
+    const int last0 = std::min(std::max(last.line0 - T.line0, 0), T.nl);
+    const int lf = fold_log(n.threads, first.nl, w), ll = fold_log(n.threads, last.nl, w);
+    return last0 == 0 ? fold_lanes(T.nl, ll, ll) : fold_lanes(last0, lf, ll);
   };
   auto lanes = [&](TileDev& T) {
     if (T.nl == 0) return;
-    T.fold = lanes_of(nominal, T);
-    T.fold1 = lanes_of(D.ts[0], T);
+    T.fold[0] = lanes_of(D.ts[0], T, 1);
+    for (int k = 1; k < 3; ++k) T.fold[k] = lanes_of(nominal, T, 1 << k);
   };
   for (TileDev& T : F.tiles) lanes(T);
   for (TileDev& T : F.tiles_by_patch) lanes(T);
@@ -782,7 +799,7 @@ void build_mat_tiles(DirPlan& D, int order, int align, int d) {
         T.line0 = l0;
         T.nl = std::min(ncp / 4, P.nlines - l0);
         T.ld = T.nl <= 4 ? 16 : 32;
-        T.fold = T.fold1 = FoldLanes{};
+        T.fold[0] = T.fold[1] = T.fold[2] = T.pad = 0;
         plds = std::max(plds, mat_lds_bytes(P.mks, T.ld, P.C, d));
         cost += (long long)(P.Lx + 64) * T.ld;
         M.tiles_by_patch.push_back(T);
@@ -801,6 +818,7 @@ void build_mat_tiles(DirPlan& D, int order, int align, int d) {
 // else they are that of ts.
 void build_tiles(DirPlan& D, bool q2, int order, int align, int d, size_t maxlds = 0) {
   for (int f = 0; f < 3; ++f) build_tileset(D.plans, D.ts[f], D.ts[f].budget, order, 1 << f, align, d);
+  D.nominal = maxlds == 0;
   for (int f = 0; f < 3; ++f) {
     // (no pass runs q1 tiles of four complex lines per grid line)
     if (maxlds && f < (q2 ? 3 : 2)) {
@@ -1471,7 +1489,9 @@ extern "C" fcsd_status fc_diff_adj(fcsd_ctx* ctx, const fcsd_set* s, int dir, in
   a.out = in_bar;
   if (nf % 4 == 0 && s->dir[dir - 1].two_rounds)
     return launch_pass(s, dir, dir == 1 ? k_fcdiff_adj2<1> : k_fcdiff_adj2<2>, a, 2);
-  return launch_pass(s, dir, dir == 1 ? k_fcdiff<1, true> : k_fcdiff<2, true>, a);
+  if (s->dir[dir - 1].nominal)
+    return launch_pass(s, dir, dir == 1 ? k_fcdiff<1, true, true> : k_fcdiff<2, true, true>, a);
+  return launch_pass(s, dir, dir == 1 ? k_fcdiff<1, true, false> : k_fcdiff<2, true, false>, a);
 }
 
 extern "C" fcsd_status fc_continue(fcsd_ctx* ctx, const fcsd_set* s, int dir, int nf, const float* in,
@@ -2097,13 +2117,13 @@ fcsd_status filter_adj_impl(fcsd_ctx* ctx, const fcsd_set* s, const float* e, co
   a.in = out_bar;
   a.u = w;
   a.out = w + 4 * pl;
-  if ((st = launch_pass(s, 2, k_filter_adj<2>, a, 2))) return st;
+  if ((st = launch_pass(s, 2, s->dir[1].nominal ? k_filter_adj<2, true> : k_filter_adj<2, false>, a, 2))) return st;
   PassArgs b = base_args(s, 1);
   b.gamma = gamma;
   b.in = w + 4 * pl;
   b.u = e;
   b.out = u_bar;
-  return launch_pass(s, 1, k_filter_adj<1>, b, 2);
+  return launch_pass(s, 1, s->dir[0].nominal ? k_filter_adj<1, true> : k_filter_adj<1, false>, b, 2);
 }
 
 // planes of a step record after the stage inputs, mu, the maximisers and the
@@ -2788,8 +2808,8 @@ fcsd_status rhs_adj_impl(fcsd_ctx* ctx, const fcsd_set* s, const float* u, const
     b.plans = D.d_plans;
     const TileSet& Q = D.ps[D.two_rounds];
     b.tiles = Q.d_tiles;
-    hipLaunchKernelGGL(D.two_rounds ? k_adjHb1<2> : k_adjHb1<1>, dim3((unsigned)Q.tiles.size()), dim3(Q.threads),
-                       Q.lds, ctx->stream, b, rhs_bar, Hb);
+    hipLaunchKernelGGL((D.two_rounds ? k_adjHb1<2, false> : D.nominal ? k_adjHb1<1, true> : k_adjHb1<1, false>),
+                       dim3((unsigned)Q.tiles.size()), dim3(Q.threads), Q.lds, ctx->stream, b, rhs_bar, Hb);
     if ((st = launch_check(ctx, "adj C"))) return st;
   }
   // the viscous q2 reverse on tiles of all four components, with the q2
@@ -2803,14 +2823,14 @@ fcsd_status rhs_adj_impl(fcsd_ctx* ctx, const fcsd_set* s, const float* u, const
     b.tiles = D.ps[1].d_tiles;
     if (wide) {
       b.tiles = D.ps[2].d_tiles;
-      hipLaunchKernelGGL(k_adjHb2w, dim3((unsigned)D.ps[2].tiles.size()), dim3(D.ps[2].threads), D.ps[2].lds,
+      hipLaunchKernelGGL((D.nominal ? k_adjHb2w<true> : k_adjHb2w<false>), dim3((unsigned)D.ps[2].tiles.size()), dim3(D.ps[2].threads), D.ps[2].lds,
                          ctx->stream, b, rhs_bar, (const float*)Hb, (const float*)d1e, (const float*)d2e, G1, mu_bar,
                          u_bar);
     } else if (visc)
-      hipLaunchKernelGGL(k_adjHb2p<true>, dim3((unsigned)D.ps[1].tiles.size()), dim3(D.ps[1].threads), D.ps[1].lds,
+      hipLaunchKernelGGL((D.nominal ? k_adjHb2p<true, true> : k_adjHb2p<true, false>), dim3((unsigned)D.ps[1].tiles.size()), dim3(D.ps[1].threads), D.ps[1].lds,
                          ctx->stream, b, rhs_bar, Hb, (const float*)d1e, (const float*)d2e, G1, G2, mu_bar, u_bar);
     else
-      hipLaunchKernelGGL(k_adjHb2p<false>, dim3((unsigned)D.ps[1].tiles.size()), dim3(D.ps[1].threads), D.ps[1].lds,
+      hipLaunchKernelGGL((D.nominal ? k_adjHb2p<false, true> : k_adjHb2p<false, false>), dim3((unsigned)D.ps[1].tiles.size()), dim3(D.ps[1].threads), D.ps[1].lds,
                          ctx->stream, b, rhs_bar, Hb, (const float*)d1e, (const float*)d2e, G1, G2, mu_bar, u_bar);
     if ((st = launch_check(ctx, "adj B2"))) return st;
   }

@@ -165,8 +165,9 @@ extern __shared__ float2 lds_z[];
 
 // ---------------------------------------------------------------- generic line ops
 
-// fc_diff / fc_diff_adj on nf fields, packed two per complex line.
-template <int DIR, bool ADJ>
+// fc_diff / fc_diff_adj on nf fields, packed two per complex line (NOM: the
+// transpose on nominal tiles, see fold_pre_t).
+template <int DIR, bool ADJ, bool NOM = true>
 __global__ void FCSD_LINE_BOUNDS k_fcdiff(PassArgs a) {
   FCSD_TILE_BEGIN(a)
   const TileMem M = tile_mem<DIR>(P, T, nl, ld);
@@ -182,7 +183,7 @@ __global__ void FCSD_LINE_BOUNDS k_fcdiff(PassArgs a) {
           M.w, [&](unsigned g) { return make_float2(at(A, g), at(B, g)); },
           [&](unsigned, unsigned l, float2 v) { at(z, l) = make_float2(v.x, two ? v.y : 0.f); });
       __syncthreads();
-      line_derivative<true>(X, Pg, P, a.gq, a.dq, a.d, T);
+      line_derivative_adj<1, 0, NOM>(X, Pg, P, a.gq, a.d, T);
     }
     float* OA = a.out + (long long)f * a.plane + M.base;
     float* OB = two ? a.out + (long long)(f + 1) * a.plane + M.base : OA;
@@ -229,7 +230,7 @@ __global__ void FCSD_LINE_BOUNDS k_fcdiff_adj2(PassArgs a) {
           at(zb, l) = make_float2(v.z, v.w);
         });
     __syncthreads();
-    line_derivative<true>(X, Pg, P, a.gq, a.dq, a.d, T, 1);
+    line_derivative_adj<2, 0, false>(X, Pg, P, a.gq, a.d, T);
     float* O = a.out + (long long)f * pl + M.base;
     walk_b<kEpiBatch>(
         M.w, [&](unsigned g) { return make_float4(at(O, g), at(O + pl, g), at(O + 2 * pl, g), at(O + 3 * pl, g)); },
@@ -762,7 +763,7 @@ __global__ void FCSD_LINE_BOUNDS k_smear(PassArgs a) {
 // (rho, rho u, rho v, theta) after the transposed q2 filter.  DIR 1: a.in
 // holds that, a.u the filter's input state (for the product of theta), out
 // the cotangent of the input state.  in may equal out.
-template <int DIR>
+template <int DIR, bool NOM>
 __global__ void FCSD_LINE_BOUNDS k_filter_adj(PassArgs a) {
   const TileDev T = a.tiles[blockIdx.x];
   if (T.nl == 0) return;
@@ -816,7 +817,7 @@ __global__ void FCSD_LINE_BOUNDS k_filter_adj(PassArgs a) {
   zero_tail(X, P);
   __syncthreads();
   if (!P.periodic) {
-    fold_pre(X, P.N, a.gf + P.gf, a.d, T);
+    fold_pre<2, 1, NOM>(X, P.N, a.gf + P.gf, a.d, T);
     __syncthreads();
   }
   fft_apply<true>(X, Pg, P);

@@ -1674,7 +1674,7 @@ __device__ __forceinline__ void flux_vjp(const float e[4], float gam, const floa
 // grid line (folded as on those of one: the same bits for either).  The
 // reverse of pass B2, which also finishes H_bar and applies the pointwise
 // reverse of H = mu grad e - f', is k_adjHb2p.
-template <int CW>
+template <int CW, bool NOM>
 __global__ void FCSD_LINE_BOUNDS k_adjHb1(PassArgs a, const float* rb, float* Hb) {
   const TileDev T = a.tiles[blockIdx.x];
   if (T.nl == 0) return;
@@ -1713,7 +1713,7 @@ __global__ void FCSD_LINE_BOUNDS k_adjHb1(PassArgs a, const float* rb, float* Hb
           for (int k = 0; k < CW; ++k) at(z + k * nl, l) = make_float2(q.mx * q.r[k], q.my * q.r[k]);
         });
     __syncthreads();
-    line_derivative<true>(X, Pg, P, a.gq, a.dq, a.d, T, 1);
+    line_derivative_adj<CW, 0, NOM>(X, Pg, P, a.gq, a.d, T);
     float* hb = Hb + (2 * comp) * pl + bo;
     walk(M.w, [&](unsigned g, unsigned l) {
 #pragma unroll
@@ -1734,7 +1734,7 @@ __global__ void FCSD_LINE_BOUNDS k_adjHb1(PassArgs a, const float* rb, float* Hb
 // which is what bounds this reverse pass (HBM traffic).  Hb (+)= D_2^T
 // (m_2x rb, m_2y rb), then G1/G2 = mu-weighted metric products (for D^T
 // later), mu_bar += H_bar . grad e, u_bar += flux VJP of -H_bar.
-template <bool VISC>
+template <bool VISC, bool NOM>
 __global__ void FCSD_LINE_BOUNDS k_adjHb2p(PassArgs a, const float* rb, float* Hb, const float* d1e,
                                             const float* d2e, float* G1, float* G2, float* mub, float* ub) {
   const TileDev T = a.tiles[blockIdx.x];
@@ -1767,7 +1767,7 @@ __global__ void FCSD_LINE_BOUNDS k_adjHb2p(PassArgs a, const float* rb, float* H
           at(zb, l) = make_float2(q.mx * q.r1, q.my * q.r1);
         });
     __syncthreads();
-    line_derivative<true>(X, Pg, P, a.gq, a.dq, a.d, T);
+    line_derivative_adj<2, 1, NOM>(X, Pg, P, a.gq, a.d, T);
     float* hb0 = Hb + (2 * comp) * pl + bo;   // x, y of comp; then of comp + 1
     const long long fo = comp * pl + bo;
     if (!VISC) {
@@ -1862,8 +1862,9 @@ __global__ void FCSD_LINE_BOUNDS k_adjHb2p(PassArgs a, const float* rb, float* H
 // lines per grid line), mu_bar and, unless mode is FLUX_VISC, the flux VJP
 // of -Hb into u_bar, so that Hb itself is never stored; then u_bar +=
 // D_2^T G2.  The same FP32 operations as k_adjHb2p followed by fc_diff_adj
-// of G2 along q2, up to the order of the tail folds' sums (FoldLanes differ
+// of G2 along q2, up to the order of the tail folds' sums (the lanes differ
 // between the tile sets).
+template <bool NOM>
 __global__ void FCSD_LINE_BOUNDS k_adjHb2w(PassArgs a, const float* rb, const float* Hb, const float* d1e,
                                           const float* d2e, float* G1, float* mub, float* ub) {
   const TileDev T = a.tiles[blockIdx.x];
@@ -1906,7 +1907,7 @@ __global__ void FCSD_LINE_BOUNDS k_adjHb2w(PassArgs a, const float* rb, const fl
         at(z3, l) = make_float2(q.mx * q.r[3], q.my * q.r[3]);
       });
   __syncthreads();
-  line_derivative<true>(X4, Pg, P, a.gq, a.dq, a.d, T);
+  line_derivative_adj<4, 2, NOM>(X4, Pg, P, a.gq, a.d, T);
   const bool flux = a.mode != FLUX_VISC;
   float* mubp = mub ? mub + bo : nullptr;
   struct VIn4 {
@@ -1964,7 +1965,7 @@ __global__ void FCSD_LINE_BOUNDS k_adjHb2w(PassArgs a, const float* rb, const fl
       });
   __syncthreads();
   // u_bar += D_2^T G2 (G2 of components 0, 1 and 2, 3 as two complex lines)
-  line_derivative<true>(X2, Pg, P, a.gq, a.dq, a.d, T);
+  line_derivative_adj<2, 1, NOM>(X2, Pg, P, a.gq, a.d, T);
   walk_b<kLoadBatch>(
       M.w,
       [&](unsigned g) {
