@@ -141,6 +141,13 @@ enum {
  * Synchronises the context's stream and drops captured step graphs.  Returns
  * FCSD_EINVAL for an out-of-range argument.  Used by the autotuner. */
 fcsd_status fcsd_set_tune(fcsd_set* set, const int lds_budget[3], const int threads[3], int order);
+/* Whether the passes' transforms run on the tiles of fcsd_set_tune (what it
+ * leaves a set on) or on a split picked for the set from an estimate, with the
+ * variants that suit it (what a new set is on).  The tuned tiles stay the
+ * nominal ones: no result changes by a bit.  Synchronises the context's
+ * stream and drops captured step graphs. */
+enum { FCSD_SPLIT_TUNED = 0, FCSD_SPLIT_PICKED = 1 };
+fcsd_status fcsd_set_split(fcsd_set* set, int split);
 
 /* How the line passes of one right-hand side or stage are launched (the
  * schedule of the four passes A, B1, B2, C of the chain-rule right-hand
@@ -183,6 +190,7 @@ typedef struct fcsd_forms {
   int32_t transforms[2]; /* patches whose q1, q2 derivatives run as transforms */
   int32_t a_two_lines;   /* transforms of pass A: tiles of two complex lines per grid line */
   int32_t b_four_lines;  /* transforms of the fused q2 pass: all eight H fields of a tile in LDS */
+  int32_t picked;        /* the transforms' split is picked for the set, not the tuned one */
   int32_t two_rounds[2]; /* transforms of four components along q1, q2 (pass C, transposes): two rounds, not four */
 } fcsd_forms;
 fcsd_status fcsd_set_forms(const fcsd_set* set, fcsd_forms* forms);

@@ -100,7 +100,8 @@ class StepArgs(ctypes.Structure):
 
 class Forms(ctypes.Structure):
     _fields_ = [("schedule", ctypes.c_int32), ("products", ctypes.c_int32 * 2), ("transforms", ctypes.c_int32 * 2),
-                ("a_two_lines", ctypes.c_int32), ("b_four_lines", ctypes.c_int32), ("two_rounds", ctypes.c_int32 * 2)]
+                ("a_two_lines", ctypes.c_int32), ("b_four_lines", ctypes.c_int32), ("picked", ctypes.c_int32),
+                ("two_rounds", ctypes.c_int32 * 2)]
 
 
 RECORD_PLANES = 66  # planes of a step record (stage inputs, mu, maximisers, pre-filter state, derivatives)
@@ -126,6 +127,7 @@ def lib():
             "fcsd_set_create": [vp, i32, P(PatchDesc), i32, i64, i32, i32, i32, P(vp)],
             "fcsd_set_destroy": [vp],
             "fcsd_set_tune": [vp, P(i32), P(i32), i32],
+            "fcsd_set_split": [vp, i32],
             "fcsd_set_schedule": [vp, i32],
             "fcsd_set_forms": [vp, P(Forms)],
             "fcsd_stage_errors": [vp, P(ctypes.c_int32)],
@@ -185,7 +187,7 @@ def lib():
 # the names every header declaration exports (checked by the CPU tests)
 EXPORTS = ["fcsd_ctx_create", "fcsd_ctx_destroy", "fcsd_ctx_set_stream", "fcsd_last_error",
            "fcsd_ctx_stream", "fcsd_ctx_sync", "fcsd_set_create", "fcsd_set_destroy", "fcsd_set_tune",
-           "fcsd_set_schedule", "fcsd_set_forms", "fcsd_stage_errors",
+           "fcsd_set_split", "fcsd_set_schedule", "fcsd_set_forms", "fcsd_stage_errors",
            "fcsd_set_filter", "fcsd_filter", "fcsd_filter_adj", "fcsd_smear", "fcsd_set_interp", "fcsd_set_walls",
            "fcsd_workspace_size", "fcsd_ext_size", "fc_continue", "fc_continue_adj", "fc_diff",
            "fc_diff_adj", "euler_rhs", "av_apply", "fcsd_rhs", "fcsd_rhs_adj", "euler_rhs_adj", "av_apply_adj",

@@ -153,6 +153,11 @@ class PatchSet:
         self.ctx.check(lib().fcsd_set_tune(self.h, b, t, int(order)), "fcsd_set_tune")
         self.tuning = (tuple(int(x) for x in budgets), tuple(int(x) for x in threads), int(order))
 
+    def set_split(self, picked: bool):
+        """Run the passes' transforms on a split picked for the set (as on a
+        new set), or on the tiles of tune()."""
+        self.ctx.check(lib().fcsd_set_split(self.h, int(bool(picked))), "fcsd_set_split")
+
     SCHED_SPLIT, SCHED_FUSED, SCHED_PERSISTENT, SCHED_FUSED_WIDE = 0, 1, 2, 3
 
     def set_schedule(self, schedule: int):
@@ -174,7 +179,7 @@ class PatchSet:
         self.ctx.check(lib().fcsd_set_forms(self.h, ctypes.byref(f)), "fcsd_set_forms")
         return {"schedule": f.schedule, "products": tuple(f.products), "transforms": tuple(f.transforms),
                 "a_two_lines": bool(f.a_two_lines), "b_four_lines": bool(f.b_four_lines),
-                "two_rounds": tuple(bool(v) for v in f.two_rounds)}
+                "picked": bool(f.picked), "two_rounds": tuple(bool(v) for v in f.two_rounds)}
 
     def stage_errors(self) -> int:
         """Read and clear the set's device error word (bit 0: a persistent

@@ -13,8 +13,8 @@ times the passes of one stage through fcsd_stage_pass with HIP events on
 the library's stream for every (budget, workgroup size) candidate under each
 launch order, picks the best candidate per tile set for the split and the
 fused schedules, times whole stages of both and of persistent candidates
-(one workgroup size and budgets that leave room for the queue slot), and
-keeps the fastest.
+(one workgroup size and budgets that leave room for the queue slot), and of the
+split that the library picks for the set by itself, and keeps the fastest.
 """
 from __future__ import annotations
 
@@ -98,7 +98,7 @@ def autotune(s, u, metric, mu, ref, gamma=1.4, dt=None, budgets=DEFAULT_BUDGETS,
             table[(order, b, t)] = tm
     # per-set picks of the split and fused schedules under each order, then
     # whole stages of each pick and of the persistent candidates
-    stage = []   # (ms, schedule, budgets, threads, order)
+    stage = []   # (ms, schedule, budgets, threads, order, picked split)
     for order in orders:
         for sched, set_passes in ((0, SET_PASSES), (1, FUSED_PASSES), (3, WIDE_PASSES)):
             if sched not in schedules:
@@ -111,7 +111,12 @@ def autotune(s, u, metric, mu, ref, gamma=1.4, dt=None, budgets=DEFAULT_BUDGETS,
                 s.set_schedule(sched)
             except api.FcsdError:
                 continue
-            stage.append((time_stage(s, bufs, reps), sched, bud, thr, order))
+            stage.append((time_stage(s, bufs, reps), sched, bud, thr, order, False))
+            if sched == 1:
+                # the split an untuned set runs on, with the variants that a
+                # tuned one does not take
+                s.set_split(True)
+                stage.append((time_stage(s, bufs, reps), sched, bud, thr, order, True))
         if 2 in schedules:
             # one workgroup size for every task of the launch; budgets of the
             # fused pick, capped for the queue slot, and uniform ones
@@ -127,9 +132,11 @@ def autotune(s, u, metric, mu, ref, gamma=1.4, dt=None, budgets=DEFAULT_BUDGETS,
                         s.set_schedule(2)
                     except api.FcsdError:
                         continue
-                    stage.append((time_stage(s, bufs, reps), 2, list(bud), [t] * 3, order))
-    ms, sched, bud, thr, order = min(stage, key=lambda r: r[0])
+                    stage.append((time_stage(s, bufs, reps), 2, list(bud), [t] * 3, order, False))
+    ms, sched, bud, thr, order, picked = min(stage, key=lambda r: r[0])
     s.tune(bud, thr, order)
+    if picked:
+        s.set_split(True)
     s.set_schedule(sched)
     if sched != 1 and 1 in schedules:
         # sets without a persistent (or wide) form run fused under its name
@@ -141,9 +148,9 @@ def autotune(s, u, metric, mu, ref, gamma=1.4, dt=None, budgets=DEFAULT_BUDGETS,
             s.set_schedule(sched)
     names = ["split", "fused", "persistent", "fused_wide"]
     return {"budgets": bud, "threads": thr, "order": "xcd" if order else "lpt", "schedule": names[sched],
-            "stage_ms": ms,
+            "split": "picked" if picked else "tuned", "stage_ms": ms,
             "stages": [{"ms": round(r[0], 4), "schedule": names[r[1]], "budgets": r[2], "threads": r[3],
-                        "order": "xcd" if r[4] else "lpt"} for r in stage],
+                        "order": "xcd" if r[4] else "lpt", "split": "picked" if r[5] else "tuned"} for r in stage],
             "table": {f"{'xcd' if o else 'lpt'}-{b // 1024}K-{t}": {["A", "B1", "B2", "C", "Bf", "Bw"][p]: round(v, 4)
                                                                    for p, v in tm.items()}
                       for (o, b, t), tm in table.items()}}

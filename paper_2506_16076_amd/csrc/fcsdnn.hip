@@ -174,6 +174,7 @@ struct fcsd_set {
   int layout = FCSD_LAYOUT_ROWS;
 
   int tile_order = FCSD_ORDER_XCD;
+  bool tuned = false;                     // by fcsd_set_tune
 
   // schedule of a stage's line passes (FCSD_SCHED_*) and the persistent
   // stage kernel's task queue
@@ -813,15 +814,28 @@ void build_mat_tiles(DirPlan& D, int order, int align, int d) {
   if (!M.tiles_by_patch.empty()) order_tiles(D.plans, M, order, pcost);
 }
 
-// align: lines per tile a multiple of it (blocked storage: 4 q1 lines, 8 q2
-// lines); maxlds > 0: the passes' splits are picked for the set (untuned),
-// else they are that of ts.
-void build_tiles(DirPlan& D, bool q2, int order, int align, int d, size_t maxlds = 0) {
+// Tile sets of a direction.  align: lines per tile a multiple of it (blocked
+// storage: 4 q1 lines, 8 q2 lines); tuned: the nominal tiles are those of
+// fcsd_set_tune (their wide q2 tiles may take the whole LDS); picked: the passes
+// run on splits picked for the set, else on the nominal ones.
+void build_tiles(DirPlan& D, bool q2, int order, int align, int d, size_t maxlds, bool tuned, bool picked) {
   for (int f = 0; f < 3; ++f) build_tileset(D.plans, D.ts[f], D.ts[f].budget, order, 1 << f, align, d);
-  D.nominal = maxlds == 0;
+  if (q2 && tuned) {
+    // q2 tiles of four complex lines per grid line (the wide fused pass, the
+    // reverse mode's q2 pass): when their tiles exceed the third budget (its
+    // smallest storage-aligned tiles do not fit), they are built for the
+    // device's whole LDS with 1024-thread workgroups
+    TileSet& W = D.ts[2];
+    if (W.lds > W.budget && W.budget < maxlds) {
+      W.budget = maxlds;
+      W.threads = 1024;
+      build_tileset(D.plans, W, W.budget, order, 4, align, d);
+    }
+  }
+  D.nominal = !picked;
   for (int f = 0; f < 3; ++f) {
     // (no pass runs q1 tiles of four complex lines per grid line)
-    if (maxlds && f < (q2 ? 3 : 2)) {
+    if (picked && f < (q2 ? 3 : 2)) {
       pick_tiles(D, f, order, align, d, maxlds);
       continue;
     }
@@ -1113,8 +1127,8 @@ extern "C" fcsd_status fcsd_set_create(fcsd_ctx* ctx, int npatch, const fcsd_pat
     for (auto& t : s->dir[dir].ts) t.budget = default_lds_budget();
     s->dir[dir].ms.budget = getenv("FCSD_LDS_BUDGET") ? default_lds_budget() : kMatBudget;
     // (a budget asked for by the environment counts as tuning)
-    build_tiles(s->dir[dir], dir == 1, s->tile_order, tile_align(layout, dir), d,
-                getenv("FCSD_LDS_BUDGET") ? 0 : (size_t)maxlds);
+    build_tiles(s->dir[dir], dir == 1, s->tile_order, tile_align(layout, dir), d, (size_t)maxlds, false,
+                !getenv("FCSD_LDS_BUDGET"));
   }
   {
     // the smallest tiles (one storage-aligned group of lines) must fit the LDS
@@ -1274,6 +1288,37 @@ extern "C" fcsd_status fcsd_set_destroy(fcsd_set* s) {
   return FCSD_OK;
 }
 
+namespace {
+
+// Tile sets, task queue and variants anew from the nominal budgets; picked: the
+// passes on splits picked for the set.  Captured steps are dropped.
+fcsd_status retile(fcsd_set* s, bool picked) {
+  fcsd_ctx* ctx = s->ctx;
+  int maxlds = 0;
+  HIPCHK(ctx, hipDeviceGetAttribute(&maxlds, hipDeviceAttributeMaxSharedMemoryPerBlock, ctx->device));
+  HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
+  for (auto& g : s->graphs)
+    if (g.exec) (void)hipGraphExecDestroy(g.exec);
+  s->graphs.clear();
+  fcsd_status r;
+  for (int dir = 0; dir < 2; ++dir) {
+    DirPlan& D = s->dir[dir];
+    build_tiles(D, dir == 1, s->tile_order, tile_align(s->layout, dir), s->d, (size_t)maxlds, s->tuned, picked);
+    if ((r = upload_tiles(ctx, D))) return r;
+  }
+  if ((r = build_stage_tasks(s))) return r;
+  s->wide_ok = s->dir[1].ts[2].lds <= (size_t)maxlds;
+  s->a_wide = pick_a_wide(s);
+  s->b_wide = pick_wide_b(s);
+  for (auto& D : s->dir) D.two_rounds = pick_two_rounds(D);
+  if ((s->schedule == FCSD_SCHED_PERSISTENT && s->stage_grid == 0) ||
+      (s->schedule == FCSD_SCHED_FUSED_WIDE && !s->wide_ok))
+    s->schedule = FCSD_SCHED_FUSED;
+  return rebuild_wall_tiles(s);
+}
+
+}  // namespace
+
 extern "C" fcsd_status fcsd_set_tune(fcsd_set* s, const int lds_budget[3], const int threads[3], int order) {
   if (!s || !lds_budget || !threads) return FCSD_EINVAL;
   fcsd_ctx* ctx = s->ctx;
@@ -1289,10 +1334,6 @@ extern "C" fcsd_status fcsd_set_tune(fcsd_set* s, const int lds_budget[3], const
       return fail(ctx, FCSD_EINVAL, "fcsd_set_tune: threads must be 64, 128, 256, 512 or 1024");
   }
   if (order != FCSD_ORDER_LPT && order != FCSD_ORDER_XCD) return fail(ctx, FCSD_EINVAL, "fcsd_set_tune: bad order");
-  HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-  for (auto& g : s->graphs)
-    if (g.exec) (void)hipGraphExecDestroy(g.exec);
-  s->graphs.clear();
   s->tile_order = order;
   // tile sets: q1 lines; q2 lines; q2 lines with two complex lines per grid line
   s->dir[0].ts[0].budget = (size_t)lds_budget[0];
@@ -1308,37 +1349,15 @@ extern "C" fcsd_status fcsd_set_tune(fcsd_set* s, const int lds_budget[3], const
   s->dir[1].ts[2].budget = (size_t)lds_budget[2];
   s->dir[1].ts[2].threads = threads[2];
   for (int dir = 0; dir < 2; ++dir) s->dir[dir].ms.budget = (size_t)lds_budget[dir ? 2 : 0];
-  fcsd_status r;
-  for (int dir = 0; dir < 2; ++dir) {
-    DirPlan& D = s->dir[dir];
-    build_tiles(D, dir == 1, order, tile_align(s->layout, dir), s->d);
-    if (dir == 1) {
-      // q2 tiles of four complex lines per grid line (the wide fused pass,
-      // the reverse mode's q2 pass): when their tiles exceed the third
-      // budget (its smallest storage-aligned tiles do not fit), they are
-      // built for the device's whole LDS with 1024-thread workgroups
-      TileSet& W = D.ts[2];
-      if (W.lds > W.budget && W.budget < (size_t)maxlds) {
-        W.budget = (size_t)maxlds;
-        W.threads = 1024;
-        build_tileset(D.plans, W, W.budget, order, 4, tile_align(s->layout, dir), s->d);
-        TileSet& R = D.ps[2];
-        R.budget = W.budget;
-        R.threads = W.threads;
-        build_tileset(D.plans, R, R.budget, order, 4, tile_align(s->layout, dir), s->d);
-      }
-    }
-    if ((r = upload_tiles(ctx, D))) return r;
-  }
-  if ((r = build_stage_tasks(s))) return r;
-  s->wide_ok = s->dir[1].ts[2].lds <= (size_t)maxlds;
-  s->a_wide = pick_a_wide(s);
-  s->b_wide = pick_wide_b(s);
-  for (auto& D : s->dir) D.two_rounds = pick_two_rounds(D);
-  if ((s->schedule == FCSD_SCHED_PERSISTENT && s->stage_grid == 0) ||
-      (s->schedule == FCSD_SCHED_FUSED_WIDE && !s->wide_ok))
-    s->schedule = FCSD_SCHED_FUSED;
-  return rebuild_wall_tiles(s);
+  s->tuned = true;
+  return retile(s, false);
+}
+
+extern "C" fcsd_status fcsd_set_split(fcsd_set* s, int split) {
+  if (!s) return FCSD_EINVAL;
+  if (split != FCSD_SPLIT_TUNED && split != FCSD_SPLIT_PICKED)
+    return fail(s->ctx, FCSD_EINVAL, "fcsd_set_split: unknown split");
+  return retile(s, split == FCSD_SPLIT_PICKED);
 }
 
 extern "C" fcsd_status fcsd_set_schedule(fcsd_set* s, int schedule) {
@@ -1373,6 +1392,7 @@ extern "C" fcsd_status fcsd_set_forms(const fcsd_set* s, fcsd_forms* f) {
     f->two_rounds[dir] = s->dir[dir].two_rounds;
   }
   f->a_two_lines = s->a_wide;
+  f->picked = !s->dir[0].nominal;
   f->b_four_lines = s->b_wide || f->schedule == FCSD_SCHED_FUSED_WIDE;
   return FCSD_OK;
 }

@@ -211,3 +211,56 @@ def test_persistent_schedule_runs_on_every_set(env, name, layout):
         s.close()
     if name == "both":
         assert 0 < prod[0] < ps.npatch and 0 < prod[1] < ps.npatch
+
+
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("tune", [(65536, 256), (16384, 256), (98304, 1024)])
+def test_tuned_set_returns_to_its_picked_split(env, tune, layout):
+    """set_split(True) gives a tuned set the variants of an untouched one and
+    the bits of its own tuning, reverse mode included; set_split(False) takes
+    them back."""
+    api, ctx, torch = env
+    cfg = CASES["few short lines"]()
+    ps = cfg.ps
+    rng = np.random.default_rng(6)
+    bar = rng.standard_normal((4, ps.plane)).astype(np.float32)
+    s = api.PatchSet.from_layout(ctx, ps, layout)
+    new = s.forms()
+    assert new["picked"]
+    s.tune(*tune)
+    tuned = s.forms()
+    assert not tuned["picked"] and not tuned["b_four_lines"] and tuned["two_rounds"] == (False, False)
+    outs = []
+    for picked in (False, True, False):
+        s.set_split(picked)
+        assert s.forms() == (new if picked else tuned)
+        u, metric = s.to_device(cfg.u0), s.to_device(ps.metric)
+        mu = s.to_device(np.full((1, ps.plane), 1e-3, np.float32))
+        rb = s.to_device(bar)
+        rhs, ub, d1 = (torch.zeros_like(u) for _ in range(3))
+        mb = torch.zeros_like(mu)
+        api.fcsd_rhs(s, u, metric, mu, cfg.ref, 1.4, rhs)
+        api.fcsd_rhs_adj(s, u, metric, mu, cfg.ref, 1.4, rb, ub, mb)
+        api.fc_diff_adj(s, 1, rb, d1, 4)
+        outs.append([s.to_host(t) for t in (rhs, ub, d1, mb)])
+    for o in outs[1:]:
+        for a, b in zip(o, outs[0]):
+            assert np.array_equal(a, b)
+    s.close()
+
+
+def test_autotuner_weighs_the_picked_split(env):
+    """The split an untouched set runs on is among the autotuner's candidates,
+    the fastest candidate is kept, and the set is left on it."""
+    from paper_2506_16076_amd import autotune
+    api, ctx, torch = env
+    cfg = CASES["few short lines"]()
+    ps = cfg.ps
+    s = api.PatchSet.from_layout(ctx, ps, 1)
+    u, metric = s.to_device(cfg.u0), s.to_device(ps.metric)
+    mu = s.to_device(np.full((1, ps.plane), 1e-3, np.float32))
+    r = autotune.autotune(s, u, metric, mu, cfg.ref, budgets=(24576, 65536), threads=(256, 512), reps=2)
+    assert {c["split"] for c in r["stages"]} == {"tuned", "picked"}
+    assert r["stage_ms"] == pytest.approx(min(c["ms"] for c in r["stages"]), abs=1e-4)
+    assert s.forms()["picked"] == (r["split"] == "picked")
+    s.close()
