@@ -128,11 +128,11 @@ enum {
  * FCSD_LDS_BUDGET environment variable at creation) and the workgroup size
  * (64, 128, 256, 512 or 1024 threads; default 256); and the launch order of
  * all tiles.  Larger budgets mean more lines per tile, fewer workgroups per
- * compute unit; larger workgroups put more threads on each line.  (The
- * passes of lines whose derivative runs as a matrix product take a fixed
- * workgroup size and, of the first or third budget, what tiles of 16 or 32
- * columns need; 80 KB unless tuned.  Until it is tuned, a set's passes run on a
- * split picked for it, with the results, bit for bit, of the default one.)  A tile
+ * compute unit; larger workgroups put more threads on each line.  (Lines
+ * whose derivative runs as a matrix product have tiles of their own, which the
+ * tuning leaves alone; it is their filter and reverse mode that run on these.
+ * Until it is tuned, a set's passes run on a split picked for it, with the
+ * results, bit for bit, of the default one, see fcsd_set_split.)  A tile
  * whose smallest storage-aligned size exceeds its budget takes more (a
  * launch takes its largest tile's LDS); the q2 tiles of four complex lines
  * per grid line (the reverse mode's q2 pass) share the
@@ -550,6 +550,13 @@ fcsd_status fcsd_stage_pass(fcsd_ctx* ctx, const fcsd_set* set, int pass, int st
                             const float* ui, float* acc, float* uout, const float* metric,
                             const float* mu, const float ref[4], float gamma, const float* dt_dev,
                             int64_t plane, void* ws, size_t ws_bytes);
+
+/* For timing and tuning: the derivatives of e - e_ref of the four state fields
+ * u by transforms on the whole tile set `tiles` of fcsd_set_tune (0: q1 lines, 1:
+ * q2 lines, 2: q2 lines with two complex lines per grid line), also of lines
+ * whose derivative otherwise runs as a matrix product.  out: [4][plane]. */
+fcsd_status fcsd_transform_pass(fcsd_ctx* ctx, const fcsd_set* set, int tiles, const float* u,
+                                const float ref[4], float* out, int64_t plane);
 
 /* Per-patch plain variant of fcsd_stage: the same kernels launched once per
  * patch (npatch launches per pass). */

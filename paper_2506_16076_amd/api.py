@@ -471,6 +471,11 @@ def fcsd_stage_pass(s, pass_id, stage, u0, ui, acc, uout, metric, mu, ref, gamma
           _f4(ref), float(gamma), _p(dt_dev), s.plane, _p(ws), ws.numel() * 4)
 
 
+def fcsd_transform_pass(s, tiles, u, ref, out):
+    _chk(u, numel=4 * s.plane), _chk(out, numel=4 * s.plane)
+    _call(s, "fcsd_transform_pass", int(tiles), _p(u), _f4(ref), _p(out), s.plane)
+
+
 class Stepper:
     """Holds the buffers of fcsd_step (state advanced in place)."""
 

@@ -15,6 +15,11 @@ launch order, picks the best candidate per tile set for the split and the
 fused schedules, times whole stages of both and of persistent candidates
 (one workgroup size and budgets that leave room for the queue slot), and of the
 split that the library picks for the set by itself, and keeps the fastest.
+
+Along a direction all of whose lines run as matrix products the stage does not
+touch the tile sets at all; the filter and the reverse mode do.  Those sets are
+picked by, and their share of a whole configuration counted as, the state's
+derivatives by transforms on them (fcsd_transform_pass).
 """
 from __future__ import annotations
 
@@ -25,6 +30,8 @@ from . import api
 SET_PASSES = ((0, 3), (2,), (1,))   # tile set -> passes timed (A+C, B2, B1)
 FUSED_PASSES = ((0, 3), (2,), (4,))  # the same with the fused B pass on the third set
 WIDE_PASSES = ((0, 3), (2,), (5,))   # the wide schedule's B pass
+TRANSFORM_PASSES = (("T0",), ("T1",), ("T2",))   # what runs on a tile set that the stage does not touch
+PASS_NAMES = {0: "A", 1: "B1", 2: "B2", 3: "C", 4: "Bf", 5: "Bw"}
 PERSISTENT_BUDGET = 163840 - 256    # leaves room for the persistent kernel's queue slot
 DEFAULT_BUDGETS = (24576, 32768, 49152, 65536, 81920, 98304, 131072, 163840)
 DEFAULT_THREADS = (256, 512, 1024)
@@ -38,13 +45,20 @@ def time_passes(s, bufs, passes, reps=3):
     # every pass reads what the passes before it wrote
     for q in range(4):
         api.fcsd_stage_pass(s, q, 1, u0, ui, acc, uout, metric, mu, ref, gamma, dt)
+
+    def run(p):
+        if p in ("T0", "T1", "T2"):
+            api.fcsd_transform_pass(s, int(p[1]), u0, ref, uout)
+        else:
+            api.fcsd_stage_pass(s, p, 1, u0, ui, acc, uout, metric, mu, ref, gamma, dt)
+
     for p in passes:
-        api.fcsd_stage_pass(s, p, 1, u0, ui, acc, uout, metric, mu, ref, gamma, dt)
+        run(p)
         e0 = torch.cuda.Event(enable_timing=True)
         e1 = torch.cuda.Event(enable_timing=True)
         e0.record(ctx.stream)
         for _ in range(reps):
-            api.fcsd_stage_pass(s, p, 1, u0, ui, acc, uout, metric, mu, ref, gamma, dt)
+            run(p)
         e1.record(ctx.stream)
         e1.synchronize()
         out[p] = e0.elapsed_time(e1) / reps
@@ -78,6 +92,15 @@ def autotune(s, u, metric, mu, ref, gamma=1.4, dt=None, budgets=DEFAULT_BUDGETS,
     if dt is None:
         dt = torch.full((1,), 1e-6, device=dev)
     bufs = (u, ui, acc, uout, metric, mu, ref, gamma, dt)
+    transforms = s.forms()["transforms"]
+    idle = tuple(k for k in range(3) if transforms[0 if k == 0 else 1] == 0)   # tile sets no stage pass runs on
+    extra = tuple(TRANSFORM_PASSES[k][0] for k in idle)
+
+    def cost():
+        """Milliseconds of the set's configuration: a stage, and the transforms
+        on the tile sets that it does not touch."""
+        return time_stage(s, bufs, reps), (sum(time_passes(s, bufs, extra, reps).values()) if extra else 0.0)
+
     cands = []
     for t in threads:
         for b in budgets:
@@ -90,7 +113,7 @@ def autotune(s, u, metric, mu, ref, gamma=1.4, dt=None, budgets=DEFAULT_BUDGETS,
     for order in orders:
         for (b, t) in cands:
             s.tune(b, t, order)
-            tm = time_passes(s, bufs, (0, 1, 2, 3, 4), reps)
+            tm = time_passes(s, bufs, (0, 1, 2, 3, 4) + extra, reps)
             try:
                 tm.update(time_passes(s, bufs, (5,), reps))
             except api.FcsdError:     # wide q2 tiles do not fit the LDS at this budget
@@ -98,11 +121,12 @@ def autotune(s, u, metric, mu, ref, gamma=1.4, dt=None, budgets=DEFAULT_BUDGETS,
             table[(order, b, t)] = tm
     # per-set picks of the split and fused schedules under each order, then
     # whole stages of each pick and of the persistent candidates
-    stage = []   # (ms, schedule, budgets, threads, order, picked split)
+    stage = []   # ((stage ms, other ms), schedule, budgets, threads, order, picked split)
     for order in orders:
         for sched, set_passes in ((0, SET_PASSES), (1, FUSED_PASSES), (3, WIDE_PASSES)):
             if sched not in schedules:
                 continue
+            set_passes = [TRANSFORM_PASSES[k] if k in idle else set_passes[k] for k in range(3)]
             pick = [min(cands, key=lambda bt: sum(table[(order,) + bt][p] for p in passes))
                     for passes in set_passes]
             bud, thr = [c[0] for c in pick], [c[1] for c in pick]
@@ -111,12 +135,15 @@ def autotune(s, u, metric, mu, ref, gamma=1.4, dt=None, budgets=DEFAULT_BUDGETS,
                 s.set_schedule(sched)
             except api.FcsdError:
                 continue
-            stage.append((time_stage(s, bufs, reps), sched, bud, thr, order, False))
+            runs = s.forms()["schedule"]
+            if runs != sched and runs in schedules:   # another one's launches, timed under its name
+                continue
+            stage.append((cost(), runs, bud, thr, order, False))
             if sched == 1:
                 # the split an untuned set runs on, with the variants that a
                 # tuned one does not take
                 s.set_split(True)
-                stage.append((time_stage(s, bufs, reps), sched, bud, thr, order, True))
+                stage.append((cost(), sched, bud, thr, order, True))
         if 2 in schedules:
             # one workgroup size for every task of the launch; budgets of the
             # fused pick, capped for the queue slot, and uniform ones
@@ -132,25 +159,19 @@ def autotune(s, u, metric, mu, ref, gamma=1.4, dt=None, budgets=DEFAULT_BUDGETS,
                         s.set_schedule(2)
                     except api.FcsdError:
                         continue
-                    stage.append((time_stage(s, bufs, reps), 2, list(bud), [t] * 3, order, False))
-    ms, sched, bud, thr, order, picked = min(stage, key=lambda r: r[0])
+                    runs = s.forms()["schedule"]
+                    if runs == 2 or runs not in schedules:
+                        stage.append((cost(), runs, list(bud), [t] * 3, order, False))
+    (ms, _), sched, bud, thr, order, picked = min(stage, key=lambda r: sum(r[0]))
     s.tune(bud, thr, order)
     if picked:
         s.set_split(True)
     s.set_schedule(sched)
-    if sched != 1 and 1 in schedules:
-        # sets without a persistent (or wide) form run fused under its name
-        s.set_schedule(1)
-        fused_ms = time_stage(s, bufs, reps)
-        if fused_ms <= 1.02 * ms:
-            ms, sched = fused_ms, 1
-        else:
-            s.set_schedule(sched)
     names = ["split", "fused", "persistent", "fused_wide"]
     return {"budgets": bud, "threads": thr, "order": "xcd" if order else "lpt", "schedule": names[sched],
             "split": "picked" if picked else "tuned", "stage_ms": ms,
-            "stages": [{"ms": round(r[0], 4), "schedule": names[r[1]], "budgets": r[2], "threads": r[3],
-                        "order": "xcd" if r[4] else "lpt", "split": "picked" if r[5] else "tuned"} for r in stage],
-            "table": {f"{'xcd' if o else 'lpt'}-{b // 1024}K-{t}": {["A", "B1", "B2", "C", "Bf", "Bw"][p]: round(v, 4)
+            "stages": [{"ms": round(r[0][0], 4), "other_ms": round(r[0][1], 4), "schedule": names[r[1]],
+                        "budgets": r[2], "threads": r[3], "order": "xcd" if r[4] else "lpt", "split": "picked" if r[5] else "tuned"} for r in stage],
+            "table": {f"{'xcd' if o else 'lpt'}-{b // 1024}K-{t}": {PASS_NAMES.get(p, p): round(v, 4)
                                                                    for p, v in tm.items()}
                       for (o, b, t), tm in table.items()}}

@@ -742,7 +742,9 @@ void pick_tiles(DirPlan& D, int f, int order, int align, int d, size_t maxlds) {
 constexpr int kMatMax = 640;
 constexpr long long kMatPoints = 8 << 20;
 
-// LDS of a matrix tile unless tuned: two workgroups per compute unit.
+// LDS of a matrix tile: two workgroups per compute unit.  The tuned budgets
+// are the transforms' (fused q2 pass of 24 patches on 48, 64, 80 and 160 KB 186,
+// 176, 143 and 143 us; of 200 patches, blocked, 688 .. 691 on any).
 constexpr size_t kMatBudget = 81920;
 
 // Row blocks (16 position pairs) and K steps (32 difference pairs) of a line.
@@ -1348,7 +1350,6 @@ extern "C" fcsd_status fcsd_set_tune(fcsd_set* s, const int lds_budget[3], const
   s->dir[0].ts[2].threads = threads[0];
   s->dir[1].ts[2].budget = (size_t)lds_budget[2];
   s->dir[1].ts[2].threads = threads[2];
-  for (int dir = 0; dir < 2; ++dir) s->dir[dir].ms.budget = (size_t)lds_budget[dir ? 2 : 0];
   s->tuned = true;
   return retile(s, false);
 }
@@ -2106,6 +2107,21 @@ extern "C" fcsd_status fcsd_stage_pass(fcsd_ctx* ctx, const fcsd_set* s, int pas
   if (ws_bytes < ws_bytes_of(s, FCSD_WS_RHS)) return fail(ctx, FCSD_EINVAL, "fcsd_stage_pass: workspace too small");
   return rhs_passes(ctx, s, ui, metric, mu, ref, gamma, mu ? FLUX_FULL : FLUX_INVISCID, MODE_RK, nullptr, stage, u0,
                     acc, uout, dt_dev, ws, -1, pass == 4 ? 6u | 16u : (pass == 5 ? 6u | 32u : 1u << pass));
+}
+
+extern "C" fcsd_status fcsd_transform_pass(fcsd_ctx* ctx, const fcsd_set* s, int tiles, const float* u,
+                                           const float ref[4], float* out, int64_t plane) {
+  fcsd_status st = check_set(ctx, s, plane);
+  if (st) return st;
+  if (tiles < 0 || tiles > 2 || !u || !ref || !out || u == out)
+    return fail(ctx, FCSD_EINVAL, "fcsd_transform_pass: bad arguments");
+  const int dir = tiles == 0 ? 1 : 2;
+  PassArgs a = base_args(s, dir);
+  set_ref(a, ref, 1.4f);
+  a.u = u;
+  a.out = out;
+  if (tiles == 2) return launch_pass(s, 2, k_dev_diff2<2>, a, 2);
+  return launch_pass(s, dir, tiles == 0 ? k_dev_diff<1> : k_dev_diff<2>, a);
 }
 
 namespace {

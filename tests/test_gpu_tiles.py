@@ -264,3 +264,47 @@ def test_autotuner_weighs_the_picked_split(env):
     assert r["stage_ms"] == pytest.approx(min(c["ms"] for c in r["stages"]), abs=1e-4)
     assert s.forms()["picked"] == (r["split"] == "picked")
     s.close()
+
+
+def test_transform_pass_times_what_the_stage_does_not_run(env):
+    """fcsd_transform_pass differentiates the state by transforms on each tile
+    set, lines of products among them: the FP64 derivative within 1e-5 of its
+    largest value (the transform's bar elsewhere), and an aliased output is
+    refused."""
+    from oracle import fcgram
+    api, ctx, torch = env
+    cfg = CASES["uneven"]()
+    ps = cfg.ps
+    s = api.PatchSet.from_layout(ctx, ps, 1)
+    assert s.forms()["transforms"] == (0, 0)
+    u = s.to_device(cfg.u0)
+    for tiles in (0, 1, 2):
+        out = torch.zeros_like(u)
+        api.fcsd_transform_pass(s, tiles, u, cfg.ref, out)
+        got = s.to_host(out)
+        for f in (0, 3):
+            want = fcgram.diff_plane(cfg.u0[f].astype(np.float64), ps, 1 if tiles == 0 else 2)
+            for p in range(ps.npatch):
+                w, g = ps.view(want, p), ps.view(got[f], p)
+                assert np.abs(g - w).max() <= 1e-5 * max(np.abs(w).max(), np.abs(cfg.u0[f]).max())
+    with pytest.raises(api.FcsdError):
+        api.fcsd_transform_pass(s, 0, u, cfg.ref, u)
+    s.close()
+
+
+def test_autotuner_times_the_transforms_of_product_sets(env):
+    """On sets of products no stage pass runs on the tuned tile sets: each is
+    picked by the transforms on it, not by passes that it cannot change."""
+    from paper_2506_16076_amd import autotune
+    api, ctx, torch = env
+    cfg = CASES["uneven"]()
+    s = api.PatchSet.from_layout(ctx, cfg.ps, 1)
+    u, metric = s.to_device(cfg.u0), s.to_device(cfg.ps.metric)
+    mu = s.to_device(np.full((1, cfg.ps.plane), 1e-3, np.float32))
+    r = autotune.autotune(s, u, metric, mu, cfg.ref, budgets=(16384, 65536), threads=(256, 512), reps=2)
+    for k, key in enumerate(("T0", "T1", "T2")):
+        best = min(v[key] for n, v in r["table"].items() if n.startswith(r["order"]))
+        assert r["table"]["%s-%dK-%d" % (r["order"], r["budgets"][k] // 1024, r["threads"][k])][key] == best \
+            or r["schedule"] == "persistent"
+    assert s.forms()["schedule"] == {"split": 0, "fused": 1, "persistent": 2}[r["schedule"]]
+    s.close()
