@@ -293,8 +293,9 @@ struct ForwardKernels {
   LineKernel mat[2], fft;
 };
 template <int DIR>
-ForwardKernels diff_kernels(LineKernel fft) {
-  return ForwardKernels{{k_mat_diff<MatSmall, DIR>, k_mat_diff<MatLarge, DIR>}, fft};
+ForwardKernels diff_kernels(LineKernel fft, int nf) {
+  if (nf <= 2) return ForwardKernels{{k_mat_diff<MatSmall, DIR, 2>, k_mat_diff<MatLarge, DIR, 2>}, fft};
+  return ForwardKernels{{k_mat_diff<MatSmall, DIR, 4>, k_mat_diff<MatLarge, DIR, 4>}, fft};
 }
 
 // Launch a forward line pass along dir over the set's tiles, or one patch's,
@@ -1494,7 +1495,8 @@ extern "C" fcsd_status fc_diff(fcsd_ctx* ctx, const fcsd_set* s, int dir, int nf
   a.nf = nf;
   a.in = in;
   a.out = out;
-  return launch_forward(s, dir, dir == 1 ? diff_kernels<1>(k_fcdiff<1, false>) : diff_kernels<2>(k_fcdiff<2, false>), a);
+  return launch_forward(
+      s, dir, dir == 1 ? diff_kernels<1>(k_fcdiff<1, false>, nf) : diff_kernels<2>(k_fcdiff<2, false>, nf), a);
 }
 
 extern "C" fcsd_status fc_diff_adj(fcsd_ctx* ctx, const fcsd_set* s, int dir, int nf, const float* out_bar,
@@ -1566,8 +1568,9 @@ RhsWs carve_rhs(const fcsd_set* s, void* ws) {
 fcsd_status launch_state_diff(const fcsd_set* s, int dir, PassArgs a, int patch = -1) {
   a.in = a.u;
   a.nf = 4;
-  if (dir == 2) return launch_forward(s, 2, diff_kernels<2>(k_dev_diff2<2>), a, patch, 2);
-  return launch_forward(s, 1, diff_kernels<1>(s->a_wide ? k_dev_diff2<1> : k_dev_diff<1>), a, patch, s->a_wide ? 2 : 1);
+  if (dir == 2) return launch_forward(s, 2, diff_kernels<2>(k_dev_diff2<2>, 4), a, patch, 2);
+  return launch_forward(s, 1, diff_kernels<1>(s->a_wide ? k_dev_diff2<1> : k_dev_diff<1>, 4), a, patch,
+                        s->a_wide ? 2 : 1);
 }
 
 // Launch a line kernel over an explicit list of n tiles of the

@@ -88,12 +88,13 @@ struct MatCtx {
   unsigned* cmax;  // [ncp]: bits of each column's largest operand
   float* side;     // [ncp]
   double* dq;      // [C + 1][2 d]
-  int ncp, lgc;    // columns (16 or 32) and their log2: 4 fields x (ncp / 4) lines, column f ncp/4 + line
+  int ncp, lgc;    // columns (16 or 32) and their log2: F fields x (ncp / F) lines, column f ncp/F + line
+  int lgn;         // log2 of the lines
   int ldw, hs;     // row stride, offset of the second half
   int KO, N, Nh, Ni, Pt;
 
   __device__ __forceinline__ int odd_row(int row) const { return ncp > 16 ? 4 * (row & 1) : 0; }
-  // word of slot n of line `line`, field 0 (field f: f ncp further)
+  // word of slot n of line `line`, field 0 (field f: 4 f ncp/F further)
   __device__ __forceinline__ int word(int n, int line) const {
     return (n >> 2) * ldw + (n & 3) + 4 * (line ^ odd_row(n >> 2));
   }
@@ -110,11 +111,13 @@ __device__ __forceinline__ int mat_tid() {
 
 __device__ __forceinline__ float* lds_f(unsigned* z) { return reinterpret_cast<float*>(z); }
 
+template <int F = 4>
 __device__ __forceinline__ MatCtx mat_setup(unsigned* lds, const PassArgs& a, const PlanDev& P, int ncp) {
   MatCtx X;
   X.z = lds;
   X.ncp = ncp;
   X.lgc = 31 - __builtin_clz(ncp);
+  X.lgn = X.lgc - (F == 4 ? 2 : 1);
   X.ldw = 4 * ncp;
   X.KO = 4 * P.mks;
   X.hs = 2 * X.KO * X.ldw;
@@ -164,7 +167,7 @@ __device__ __forceinline__ MatThread mat_thread(const MatCtx& X, const PlanDev& 
     g = 4u * (unsigned)(pi * P.n1 + ln), gpb = 16u * P.n1, glg = 32u;
   }
   // line groups: a power of two, no more than the workgroup's 32-thread slots
-  const int lgG = max(X.lgc - 2 - lgl, 0);
+  const int lgG = max(X.lgn - lgl, 0);
   const int lg = slot & ((1 << lgG) - 1), PS = (int)(blockDim.x >> 5) >> lgG;
   M.line = (lg << lgl) + ln;
   M.stop = M.line < nl ? X.N : 0;
@@ -573,14 +576,37 @@ __global__ void __launch_bounds__(256) k_mat_table(const MatTab* tabs, const dou
 // ---------------------------------------------------------------- passes
 
 // Derivative along DIR of nf fields (fc_diff; pass A and the reverse mode's
-// derivatives of the state), four fields a round.
-template <class CLS, int DIR>
+// derivatives of the state), F a round.  Of one or two fields F is 2, on 16
+// columns for the eight lines: on 32 they would load and multiply three or two
+// copies of a field (one field along q2 of 100 patches of 128 .. 512 points 130 ->
+// 107 us, of 24 patches 56 -> 46; transforms 117 and 50).
+template <class CLS, int DIR, int F>
 __device__ __forceinline__ void mat_diff_tile(const PassArgs& a, const TileDev& T, unsigned* lds) {
   const PlanDev P = a.plans[T.plan];
-  const MatCtx X = mat_setup(lds, a, P, T.ld);
+  const MatCtx X = mat_setup<F>(lds, a, P, F == 2 ? 16 : T.ld);
   const MatThread M = mat_thread<DIR>(X, P, T.nl);
   const long long base = P.off + tile_first<DIR>(T.line0, P.nb1, P.n1), pl = a.plane;
   __syncthreads();
+  if constexpr (F == 2) {
+    const bool two = a.nf > 1;
+    const float *A = a.in + base, *B = two ? A + pl : A;
+    float* z = lds_f(X.z);
+    mat_walk<2 * CLS::load>(
+        X, M, [&](unsigned g) { return make_float2(at(A, g), at(B, g)); },
+        [&](unsigned, int w, float2 v) {
+          z[w] = v.x;
+          z[w + 2 * 16] = v.y;
+        });
+    mat_apply<CLS>(X, P, a.mt, a.d);
+    float* O = a.out + base;
+    mat_walk<4>(
+        X, M, [](unsigned) { return 0; },
+        [&](unsigned g, int w, int) {
+          at(O, g) = z[w];
+          if (two) at(O + pl, g) = z[w + 2 * 16];
+        });
+    return;
+  }
   for (int f = 0; f < a.nf; f += 4) {
     const float* A = a.in + (long long)f * pl + base;
     const int n = min(4, a.nf - f);
@@ -791,9 +817,9 @@ __device__ __forceinline__ void mat_C_tile(const PassArgs& a, const TileDev& T, 
   unsigned* lds = reinterpret_cast<unsigned*>(lds_z); \
   call(a, T, lds);
 
-template <class CLS, int DIR>
+template <class CLS, int DIR, int F>
 __global__ void FCSD_MAT_BOUNDS(CLS) k_mat_diff(PassArgs a) {
-  FCSD_MAT_KERNEL((mat_diff_tile<CLS, DIR>))
+  FCSD_MAT_KERNEL((mat_diff_tile<CLS, DIR, F>))
 }
 template <class CLS, bool FUSED>
 __global__ void FCSD_MAT_BOUNDS(CLS) k_mat_B(PassArgs a) {
@@ -881,7 +907,7 @@ __device__ __forceinline__ void stage_tasks(const StageArgs& s) {
     if constexpr (MAT) {
       if (mat) {
         if (kind == TASK_A) {
-          if (!s.skipA) mat_diff_tile<MatLarge, 1>(s.A, T, mlds);
+          if (!s.skipA) mat_diff_tile<MatLarge, 1, 4>(s.A, T, mlds);
         } else if (kind == TASK_B) {
           mat_B_tile<MatLarge, true>(s.B, T, mlds);
         } else {

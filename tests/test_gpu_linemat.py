@@ -182,3 +182,36 @@ def test_nearly_uniform_lines(env, d, N, amp):
     print("d", d, "N", N, "amp", amp, "rel L2", err, "bar", tol, flush=True)
     assert err <= tol
     s.close()
+
+
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("d,C,sides", [
+    (5, 27, [(11, 13), (17, 31), (256, 34)]),
+    (2, 28, [(511, 17), (18, 512), (257, 12)]),
+    (5, 27, [(513, 20), (40, 100)]),
+    (5, 0, [(30, 64), (49, 12)]),
+])
+def test_any_number_of_fields_gives_the_same_bits(env, d, C, sides, layout):
+    """One or two fields run on narrower tiles than three and more: the bits of
+    a field do not depend on how many others are differentiated with it."""
+    api, ctx, torch = env
+    rng = np.random.default_rng(9)
+    s, off, plane = make(api, ctx, sides, d, C, layout)
+    for direction in (1, 2):
+        inp, idx = place([lines(rng, 5, b, a, direction) for a, b in sides], None, off, plane, layout)
+        ti = torch.from_numpy(inp.reshape(-1)).cuda()
+        outs = {}
+        for nf in (1, 2, 3, 5):
+            to = torch.full((nf * plane,), 7.0, device="cuda:0")
+            api.fc_diff(s, direction, ti, to, nf)
+            outs[nf] = to.cpu().numpy().reshape(nf, plane)
+        for k, side in zip(idx, sides):
+            pairs = side[direction - 1] > 512    # transforms take two fields as one complex line
+            for nf in (1, 2, 3):
+                n = nf // 2 * 2 if pairs else nf
+                assert np.array_equal(outs[nf][:n, k.ravel()], outs[5][:n, k.ravel()])
+        inside = np.zeros(plane, bool)
+        for k in idx:
+            inside[k.ravel()] = True
+        assert np.all(outs[1][:, ~inside] == 7.0) and not np.any(outs[1][:, inside] == 7.0)
+    s.close()
