@@ -104,6 +104,11 @@ enum {
  * lines does not fit a workgroup's LDS), computes the FC-Gram continuation matrices
  * (Sec. 2.2, eq. continuation) in binary128 arithmetic, the FP32 twiddle
  * and derivative-multiplier tables and the tile schedules, and uploads them.
+ * A line's derivative runs as a transform or, on sets of independent patches,
+ * for lines of up to 512 points as a matrix product (q1 lines with a
+ * 13-smooth L only on sets of at most 8 M points): a patch's results differ in
+ * their rounding between sets on either side of such a line, never with a
+ * set's tuning or schedule.
  * `ring_sectors` / `ring_shells` > 0 declare the index-aligned annulus
  * layout (sector s of shell k is patch k*ring_sectors + s, neighbours overlap
  * by 2 n_v + 1 = 19 lines) used by the fringe exchange and by the

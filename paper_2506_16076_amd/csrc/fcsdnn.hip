@@ -727,19 +727,27 @@ void pick_tiles(DirPlan& D, int f, int order, int align, int d, size_t maxlds) {
 // Lines whose derivative runs as a matrix product (linemat.h), a rule on the
 // set and the line, so that every tiling, schedule and entry point of a set
 // computes the same bits:
-//   - extensions of up to kMatMax points (the work grows with the length, the
-//     transform's with its logarithm);
+//   - lines of up to 512 samples (the row blocks that the kernels hold:
+//     mat_size_fits) and kMatMax extension points (the work grows with the
+//     length, the transform's with its logarithm);
 //   - q1 lines of sets of at most kMatPoints points, and those whose length has
 //     no radix plan (their transform is twice as long): passes A and C of 3.9 M
 //     points take 51 .. 70 ps a point as products against 61 .. 79 as
 //     transforms (sides 101 .. 512), of the 15.8 M points of 200 uneven patches
 //     829 against 772 us (there the transform's larger tiles fill the chip, and
-//     the products stream their tables from beyond L2); q2 lines of any set (pass B: 703 against 724 us there, 43
-//     .. 60 against 52 .. 71 ps a point at 3.9 M);
+//     the products stream their tables from beyond L2); the line lies between
+//     the two sizes, none in between was measured;
+//   - q2 lines of any set (fused pass B: 685 against 720 us there, 43 .. 60
+//     against 52 .. 71 ps a point at 3.9 M; their derivative alone, which the
+//     reverse mode recomputes, is the transform's gain there, 250 against 231
+//     us, and stays a product for its bits);
 //   - not on index-aligned annulus sets: the derivative with respect to a
 //     boundary parameter that their reverse mode accumulates is a 64-bit
-//     result, reproduced to 1e-9, and any other rounding of the lines moves
-//     it by 1e-8.
+//     result and moves by 1e-8 with any other rounding of the lines.  (It is a
+//     sum over FP32 lines, no more accurate in one form than in the other; the
+//     rule keeps results, it gives up no known time: steps of 16 x 128 x 128
+//     and 128 x 101 x 101 points measured 530 and 1130 us with products, 524
+//     and 1030 on the transforms' picked split.)
 constexpr int kMatMax = 640;
 constexpr long long kMatPoints = 8 << 20;
 
@@ -769,7 +777,8 @@ bool mat_line(int N, int C, int d, int align, size_t maxlds) {
 // without a second tile (the table streams once per tile, so wide tiles are
 // better where there are enough of them: right-hand side of 24 patches, about
 // 850 tiles a direction, 342 us with 32 columns, 479 with 16; one derivative
-// of 24 small patches, 370 tiles, 44 us with 32, 38 with 16).  The kernels for
+// of 24 small patches, 370 tiles, 44 us with 32, 38 with 16; the line is two
+// tiles a compute unit, between these).  The kernels for
 // large lines run all of a set's lines when it has such lines: two launches a
 // pass each end in a partly filled chip (that right-hand side 415 us).
 void build_mat_tiles(DirPlan& D, int order, int align, int d) {
@@ -1562,9 +1571,8 @@ RhsWs carve_rhs(const fcsd_set* s, void* ws) {
   return RhsWs{w, w + 4 * pl, w + 12 * pl};
 }
 
-// flux: FLUX_FULL, FLUX_VISC, FLUX_INVISCID ; out: MODE_SET / MODE_ADD / MODE_RK
-// e - e_ref of the four state fields differentiated along dir into a.out
-// (pass A, and the reverse mode's derivatives).
+// The four state fields differentiated along dir into a.out (pass A, and the
+// reverse mode's derivatives); transforms subtract e_ref, products need not.
 fcsd_status launch_state_diff(const fcsd_set* s, int dir, PassArgs a, int patch = -1) {
   a.in = a.u;
   a.nf = 4;
@@ -1621,6 +1629,7 @@ fcsd_status wall_theta_derivs(fcsd_ctx* ctx, const fcsd_set* s, const float* u, 
   return launch_check(ctx, "wall theta derivatives");
 }
 
+// flux: FLUX_FULL, FLUX_VISC, FLUX_INVISCID ; out: MODE_SET / MODE_ADD / MODE_RK
 fcsd_status rhs_passes(fcsd_ctx* ctx, const fcsd_set* s, const float* u, const float* metric, const float* mu,
                        const float ref[4], float gamma, int flux, int outmode, float* rhs, int stage,
                        const float* u0, float* acc, float* uout, const float* dtp, void* ws, int patch,
@@ -1720,7 +1729,9 @@ fcsd_status rhs_passes(fcsd_ctx* ctx, const fcsd_set* s, const float* u, const f
       }
     }
     if ((passes & 2u) && !fuse)
-      if ((st = launch_forward(s, 2, ForwardKernels{{k_mat_B<MatSmall, false>, k_mat_B<MatLarge, false>}, k_passB1}, b, patch, 2))) return st;
+      if ((st = launch_forward(s, 2, ForwardKernels{{k_mat_B<MatSmall, false>, k_mat_B<MatLarge, false>}, k_passB1},
+                               b, patch, 2)))
+        return st;
   }
   if (fuse) {
     if ((st = launch_forward(s, 2,
@@ -1729,7 +1740,8 @@ fcsd_status rhs_passes(fcsd_ctx* ctx, const fcsd_set* s, const float* u, const f
                              b, patch, wide ? 4 : 2)))
       return st;
   } else if (passes & 4u) {
-    if ((st = launch_forward(s, 2, ForwardKernels{{k_mat_B2<MatSmall>, k_mat_B2<MatLarge>}, k_passB2}, a, patch))) return st;
+    if ((st = launch_forward(s, 2, ForwardKernels{{k_mat_B2<MatSmall>, k_mat_B2<MatLarge>}, k_passB2}, a, patch)))
+      return st;
   }
   if (!(passes & 8u)) return FCSD_OK;
   const bool two = s->dir[0].two_rounds;

@@ -976,7 +976,7 @@ __device__ __forceinline__ void passC2_tile(const PassArgs& a, const TileDev& T,
   T2.nl = 2 * T.nl;
   const LineCtx X = line_setup(lds, T2, P, a.tw, a.km);
   float2* __restrict__ z = X.z;
-  const int N = P.N, nl = T.nl, ld = T.ld;
+  const int nl = T.nl, ld = T.ld;
   const TileMem M = tile_mem<1>(P, T, nl, ld);
   const long long pl = a.plane;
   float dt = 0.f;
@@ -985,7 +985,6 @@ __device__ __forceinline__ void passC2_tile(const PassArgs& a, const TileDev& T,
   const float* m1x = a.metric + M.base;
   const float* m1y = a.metric + pl + M.base;
   float2* __restrict__ zb = z + nl;
-  (void)N;
   __syncthreads();
   for (int comp = 0; comp < 4; comp += 2) {
     const float* A = a.H + (2 * comp) * pl + M.base;

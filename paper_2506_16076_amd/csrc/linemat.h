@@ -1,5 +1,5 @@
 // Line derivatives as matrix products on the fp16 matrix cores, at FP32
-// accuracy (lines of up to kMatMax extension points).
+// accuracy (lines of up to 512 samples, 640 with their continuation).
 //
 // The FC derivative of a line is K Delta ext: Delta ext the L cyclic first
 // differences of the extension (engine.h), K the N x L section of the
@@ -250,14 +250,14 @@ __device__ __forceinline__ mhalf8 mat_half8(const uint4& v) {
 }
 
 // Products of TR row blocks (16 position pairs each, from rb0) with TC column
-// blocks (16 columns, from column c0): acc[tr][e/o][tc].  The table comes from
+// blocks (16 columns): acc[tr][e/o][tc].  The table comes from
 // L2 (or beyond, for the first tile of a patch on its die), a latency of one or
 // two thousand cycles under the passes' own traffic: its words are read D half
 // K steps (the even or the odd part) ahead.  Row blocks past RB repeat
 // the last one (not stored).
 template <int TR, int TC, int D>
-__device__ __forceinline__ void mat_gemm(const uint4* __restrict__ tab, int KS, int rb0, int RB, int c0,
-                                         const MatCtx& X, mfloat4 (&acc)[TR][2][TC]) {
+__device__ __forceinline__ void mat_gemm(const uint4* __restrict__ tab, int KS, int rb0, int RB, const MatCtx& X,
+                                         mfloat4 (&acc)[TR][2][TC]) {
   const int lane = mat_tid() & 63;
   const unsigned lo16 = 16u * lane;
   const uint4* ap[TR];  // uniform
@@ -277,14 +277,13 @@ __device__ __forceinline__ void mat_gemm(const uint4* __restrict__ tab, int KS, 
     for (int h = 0; h < 2; ++h)
 #pragma unroll
       for (int c = 0; c < TC; ++c) acc[r][h][c] = mfloat4{0.f, 0.f, 0.f, 0.f};
-  const int col = c0 + (lane & 15), ldw = X.ldw;
+  const int col = lane & 15, ldw = X.ldw;
   const unsigned* bh = X.z + 2 * (lane >> 4) * ldw + 4 * col;
   const unsigned* bl = X.z + (2 * (lane >> 4) + 1) * ldw + 4 * (col ^ X.odd_row(1));
   for (int s0 = 0; s0 <= last; s0 += D) {
 #pragma unroll
     for (int j = 0; j < D; ++j) {
       const int h = j & 1;
-      if (D > 2 && j == 2 && s0 + j > last) break;  // an odd number of K steps
       mhalf8 b[2][TC];
 #pragma unroll
       for (int c = 0; c < TC; ++c) {
@@ -314,19 +313,18 @@ __device__ __forceinline__ void mat_gemm(const uint4* __restrict__ tab, int KS, 
 template <int TR, int TC, int D>
 __device__ __forceinline__ void mat_product(const MatCtx& X, const PlanDev& P, const uint4* __restrict__ mt) {
   const int tid = mat_tid(), lane = tid & 63;
-  // TR row blocks per wave (mat_tile_fits), all columns
+  // TR row blocks per wave, all columns
   const int RB = P.mrb, rb0 = __builtin_amdgcn_readfirstlane(tid >> 6) * TR;
-  constexpr int c0 = 0;
   const bool on = rb0 < RB;
   mfloat4 acc[TR][2][TC];
-  if (on) mat_gemm<TR, TC, D>(mt + P.mt, P.mks, rb0, RB, c0, X, acc);
+  if (on) mat_gemm<TR, TC, D>(mt + P.mt, P.mks, rb0, RB, X, acc);
   __syncthreads();  // every operand has been read: the results take their places
   if (on) {
     const unsigned* cm = X.cmax;
     float* z = lds_f(X.z);
 #pragma unroll
     for (int c = 0; c < TC; ++c) {
-      const int col = c0 + 16 * c + (lane & 15);
+      const int col = 16 * c + (lane & 15);
       const int e = -(mat_scale(cm[col]) + P.mes);
       float* oc = z + (4 * rb0 + (lane >> 4)) * X.ldw + 4 * (col ^ X.odd_row(lane >> 4));
 #pragma unroll
@@ -484,22 +482,18 @@ __device__ __forceinline__ void mat_apply(const MatCtx& X, const PlanDev& P, con
     }
   }
   __syncthreads();
-  // row blocks per wave
+  // one or two row blocks per wave (CLS::rows, mat_size_fits)
   constexpr int W = CLS::threads / 64, D = CLS::ahead;
   if (ncp == 16) {
     if (P.mrb <= W)
       mat_product<1, 1, D>(X, P, mt);
-    else if (P.mrb <= 2 * W)
+    else
       mat_product<2, 1, D>(X, P, mt);
-    else if constexpr (CLS::rows > 2)
-      mat_product<4, 1, D>(X, P, mt);
   } else {
     if (P.mrb <= W)
       mat_product<1, 2, D>(X, P, mt);
-    else if (P.mrb <= 2 * W)
+    else
       mat_product<2, 2, D>(X, P, mt);
-    else if constexpr (CLS::rows > 2)
-      mat_product<4, 2, D>(X, P, mt);
   }
   __syncthreads();
 }
