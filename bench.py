@@ -76,8 +76,20 @@ def recorded_traffic(kernel, npts):
 # again (FP32)
 FILTER_BYTES = 64
 
-PASS_KERNEL = {"A": "k_dev_diff2<1>", "B1": "k_mat_B", "B2": "k_mat_B2", "C": "k_passC", "Bf": "k_mat_B",
-               "Bw": "k_mat_B", "stage": "k_stage"}
+
+def pass_kernels(forms):
+    """Kernel of each pass (Bw: the wide schedule's q2 pass), from what the
+    set's lines run as; sets of both kinds of lines: the transforms'."""
+    q1 = forms["transforms"][0] > 0
+    q2 = forms["transforms"][1] > 0
+    return {"A": ("k_dev_diff2<1>" if forms["a_two_lines"] else "k_dev_diff<1>") if q1 else "k_mat_diff",
+            "B1": "k_passB1" if q2 else "k_mat_B", "B2": "k_passB2" if q2 else "k_mat_B2",
+            "Bf": ("k_passB4" if forms["b_four_lines"] else "k_passB") if q2 else "k_mat_B",
+            "Bw": "k_passB4" if q2 else "k_mat_B",
+            "C": ("k_passC2" if forms["two_rounds"][0] else "k_passC") if q1 else "k_mat_C",
+            "stage": "k_stage" if q1 and q2 and forms["products"] == (0, 0) else "k_stage_mat"}
+
+
 # passes of a stage under each schedule (Bf: passes B1 and B2 in one launch)
 SCHED_PASSES = {"split": ["A", "B1", "B2", "C"], "fused": ["A", "Bf", "C"], "persistent": ["A", "Bf", "C"],
                 "fused_wide": ["A", "Bw", "C"]}
@@ -299,7 +311,7 @@ def main():
         r = autotune.autotune(ss, uu, mm, mu0, ref, 1.4, budgets=tuple(sorted(set(tuning["budgets"]) | {163840})),
                               threads=tuple(sorted(set(tuning["threads"]) | {1024})), orders=(order,),
                               schedules=(0, 1, 3))
-        aux_tuning[name] = {k: r[k] for k in ("budgets", "threads", "order", "schedule", "stage_ms")}
+        aux_tuning[name] = {k: r[k] for k in ("budgets", "threads", "order", "schedule", "split", "stage_ms")}
     st = api.Stepper(s, u, metric, cfg.ref, W=W)
 
     # ---------------- full step, graph replay
@@ -399,7 +411,8 @@ def main():
         dom = max(used, key=passes.get)
     achieved = pass_gb[dom] / (passes[dom] / 1e3)
     stage_bytes = sum(pass_gb[n] for n in used) * 1e9 / npts
-    traffic = recorded_traffic(PASS_KERNEL[dom], npts)
+    kernels = pass_kernels(s.forms())
+    traffic = recorded_traffic(kernels[dom], npts)
 
     # ---------------- per-step spectral filter (paper Sec. 4.3.1, alpha 10,
     # p 14), timed on its own: two line passes over the state in place
@@ -658,7 +671,7 @@ def main():
                    "layout": args.layout,
                    "points": npts, "patches": ps.npatch},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "kernel": PASS_KERNEL[dom],
+                     "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "kernel": kernels[dom],
                      "bytes_per_point": pass_gb[dom] * 1e9 / npts, "ms": passes[dom],
                      "note": "achieved = algorithmic bytes of the kernel averaged over the five stages / "
                              "its mean launch time (HIP events on the library stream)"},
