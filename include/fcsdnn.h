@@ -120,7 +120,8 @@ fcsd_status fcsd_set_create(fcsd_ctx* ctx, int npatch, const fcsd_patch_desc* pa
                             int d, int64_t plane, int ring_sectors, int ring_shells,
                             int layout, fcsd_set** out);
 fcsd_status fcsd_set_destroy(fcsd_set* set);
-/* Launch order of the batched line tiles. */
+/* Launch order of the batched line tiles (those of lines that run as matrix
+ * products, which read a table per patch, are always dealt by patch). */
 enum {
   FCSD_ORDER_LPT = 0, /* longest tile first over all patches */
   FCSD_ORDER_XCD = 1  /* whole patches dealt to the 8 dies (one L2 each),

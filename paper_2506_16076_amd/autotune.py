@@ -66,19 +66,23 @@ def time_passes(s, bufs, passes, reps=3):
 
 
 def time_stage(s, bufs, reps=3):
-    """Mean milliseconds of one whole stage (stage 1) under the set's
-    current schedule."""
+    """Milliseconds of one whole stage (stage 1) under the set's current
+    schedule: the best mean of three batches (single ones differ by 3 %, more
+    than launch orders do)."""
     u0, ui, acc, uout, metric, mu, ref, gamma, dt = bufs
     ctx = s.ctx
     api.fcsd_stage(s, 1, u0, ui, acc, uout, metric, mu, ref, gamma, dt)
-    e0 = torch.cuda.Event(enable_timing=True)
-    e1 = torch.cuda.Event(enable_timing=True)
-    e0.record(ctx.stream)
-    for _ in range(reps):
-        api.fcsd_stage(s, 1, u0, ui, acc, uout, metric, mu, ref, gamma, dt)
-    e1.record(ctx.stream)
-    e1.synchronize()
-    return e0.elapsed_time(e1) / reps
+    best = float("inf")
+    for _ in range(3):
+        e0 = torch.cuda.Event(enable_timing=True)
+        e1 = torch.cuda.Event(enable_timing=True)
+        e0.record(ctx.stream)
+        for _ in range(reps):
+            api.fcsd_stage(s, 1, u0, ui, acc, uout, metric, mu, ref, gamma, dt)
+        e1.record(ctx.stream)
+        e1.synchronize()
+        best = min(best, e0.elapsed_time(e1) / reps)
+    return best
 
 
 def autotune(s, u, metric, mu, ref, gamma=1.4, dt=None, budgets=DEFAULT_BUDGETS, threads=DEFAULT_THREADS,

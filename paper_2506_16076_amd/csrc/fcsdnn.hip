@@ -780,8 +780,11 @@ bool mat_line(int N, int C, int d, int align, size_t maxlds) {
 // of 24 small patches, 370 tiles, 44 us with 32, 38 with 16; the line is two
 // tiles a compute unit, between these).  The kernels for
 // large lines run all of a set's lines when it has such lines: two launches a
-// pass each end in a partly filled chip (that right-hand side 415 us).
-void build_mat_tiles(DirPlan& D, int order, int align, int d) {
+// pass each end in a partly filled chip (that right-hand side 415 us).  Patches
+// are dealt to the dies whatever the tuned order: a patch's tiles then share
+// their table in one die's L2 (fused q2 pass of 24 row-major patches 143 us,
+// longest tile first 255; of 200 blocked ones 690 and 748).
+void build_mat_tiles(DirPlan& D, int align, int d) {
   const int least = mat_min_columns(align);
   TileSet& M = D.ms;
   size_t ntiles = 0;
@@ -823,7 +826,7 @@ void build_mat_tiles(DirPlan& D, int order, int align, int d) {
     M.lds = std::max(M.lds, plds);
     pcost.push_back(cost);
   }
-  if (!M.tiles_by_patch.empty()) order_tiles(D.plans, M, order, pcost);
+  if (!M.tiles_by_patch.empty()) order_tiles(D.plans, M, FCSD_ORDER_XCD, pcost);
 }
 
 // Tile sets of a direction.  align: lines per tile a multiple of it (blocked
@@ -856,7 +859,7 @@ void build_tiles(DirPlan& D, bool q2, int order, int align, int d, size_t maxlds
     D.ps[f].estimate = 0.0;
     build_tileset(D.plans, D.ps[f], D.ps[f].budget, order, 1 << f, align, d);
   }
-  build_mat_tiles(D, order, align, d);
+  build_mat_tiles(D, align, d);
 }
 
 int tile_align(int layout, int dir) { return layout == FCSD_LAYOUT_B8X4 ? (dir == 0 ? 4 : 8) : 1; }
